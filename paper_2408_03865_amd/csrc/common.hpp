@@ -21,6 +21,14 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// 16-byte vectors at any element's address.  gfx950 loads and stores them there in one
+// instruction (the HSA runtime runs in unaligned access mode), so a row whose length is
+// no multiple of the vector, and with it every row but the first, takes the same code as
+// an aligned one.
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
+typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
+typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
+
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
@@ -34,6 +42,7 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
 template <typename T> struct Storage;
 
 template <> struct Storage<float> {
+    typedef u32x4_a4 Vec;
     static constexpr int kBytes = 4;
     static constexpr int kPerVec = 4;     // elements per 16-byte vector
     __device__ static float load1(const float* p) { return *p; }
@@ -50,6 +59,7 @@ template <> struct Storage<float> {
 };
 
 template <> struct Storage<bf16_t> {
+    typedef u32x4_a2 Vec;
     static constexpr int kBytes = 2;
     static constexpr int kPerVec = 8;
     __device__ static float load1(const bf16_t* p) { return __uint_as_float((uint32_t)p->bits << 16); }
@@ -68,19 +78,18 @@ template <> struct Storage<bf16_t> {
 };
 
 // Load K consecutive elements starting at row[l0] (K a multiple of the vector width),
-// converting to float; elements at or beyond L read as `fill`.  `vec` says the row
-// base is 16-byte aligned and L is a multiple of the vector width.
-// With FULL the caller guarantees l0 + K <= L and vector alignment, so the loads are
-// unconditional (no control flow: the compiler can batch them and defer the waits).
+// converting to float; elements at or beyond L read as `fill`.  With FULL the caller
+// guarantees l0 + K <= L, so the loads are unconditional (no control flow: the compiler
+// can batch them and defer the waits).
 template <typename T, int K, bool FULL = false>
-__device__ __forceinline__ void load_run(const T* __restrict__ row, int64_t l0, int64_t L, bool vec,
-                                         float* v, float fill = 0.0f) {
+__device__ __forceinline__ void load_run(const T* __restrict__ row, int64_t l0, int64_t L, float* v,
+                                         float fill = 0.0f) {
     constexpr int PV = Storage<T>::kPerVec;
     static_assert(K % PV == 0, "K must be a multiple of the vector width");
-    if (FULL || (vec && l0 + K <= L)) {
+    if (FULL || l0 + K <= L) {
 #pragma unroll
         for (int i = 0; i < K / PV; ++i) {
-            const u32x4 w = *reinterpret_cast<const u32x4*>(row + l0 + i * PV);
+            const u32x4 w = *reinterpret_cast<const typename Storage<T>::Vec*>(row + l0 + i * PV);
             Storage<T>::unpack(w, v + i * PV);
         }
     } else {
@@ -89,8 +98,7 @@ __device__ __forceinline__ void load_run(const T* __restrict__ row, int64_t l0, 
     }
 }
 
-// K consecutive elements at row[l0] as raw 16-byte vectors (l0 + K <= L, vector
-// aligned), converted later by unpack_run: the loads can be issued well before the
+// K consecutive elements at row[l0] as raw 16-byte vectors (l0 + K <= L), converted later by unpack_run: the loads can be issued well before the
 // values are needed, e.g. ahead of a barrier.
 template <typename T, int K>
 struct RawRun {
@@ -101,7 +109,7 @@ __device__ __forceinline__ RawRun<T, K> load_raw(const T* __restrict__ row, int6
     constexpr int PV = Storage<T>::kPerVec;
     RawRun<T, K> r;
 #pragma unroll
-    for (int i = 0; i < K / PV; ++i) r.w[i] = *reinterpret_cast<const u32x4*>(row + l0 + i * PV);
+    for (int i = 0; i < K / PV; ++i) r.w[i] = *reinterpret_cast<const typename Storage<T>::Vec*>(row + l0 + i * PV);
     return r;
 }
 // The same, non-temporal: for inputs read once, so that they do not take cache space
@@ -112,7 +120,7 @@ __device__ __forceinline__ RawRun<T, K> load_raw_nt(const T* __restrict__ row, i
     RawRun<T, K> r;
 #pragma unroll
     for (int i = 0; i < K / PV; ++i)
-        r.w[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(row + l0 + i * PV));
+        r.w[i] = __builtin_nontemporal_load(reinterpret_cast<const typename Storage<T>::Vec*>(row + l0 + i * PV));
     return r;
 }
 template <typename T, int K>
@@ -131,13 +139,12 @@ __device__ __forceinline__ void unpack_run(const RawRun<T, K>& r, float* v) {
 // otherwise (non-temporal, the fp32 conv backward's dx ran 40% slower, while the fp32
 // scan backward's outputs gained 2%).
 template <typename T, int K, bool FULL = false, bool NT = (K == Storage<T>::kPerVec)>
-__device__ __forceinline__ void store_run(T* __restrict__ row, int64_t l0, int64_t L, bool vec,
-                                          const float* v) {
+__device__ __forceinline__ void store_run(T* __restrict__ row, int64_t l0, int64_t L, const float* v) {
     constexpr int PV = Storage<T>::kPerVec;
-    if (FULL || (vec && l0 + K <= L)) {
+    if (FULL || l0 + K <= L) {
 #pragma unroll
         for (int i = 0; i < K / PV; ++i) {
-            u32x4* dst = reinterpret_cast<u32x4*>(row + l0 + i * PV);
+            auto* dst = reinterpret_cast<typename Storage<T>::Vec*>(row + l0 + i * PV);
             if constexpr (NT) __builtin_nontemporal_store(Storage<T>::pack(v + i * PV), dst);
             else *dst = Storage<T>::pack(v + i * PV);
         }

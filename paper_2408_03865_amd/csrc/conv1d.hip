@@ -22,14 +22,13 @@ constexpr int kTokBwd = 8;     // tokens per thread per step (backward)
 constexpr int kThreads = 256;
 
 // N position indices from l0 (N a multiple of 4); beyond L they read 0.  FULL: the
-// caller guarantees l0 + N <= L and 16-byte alignment
+// caller guarantees l0 + N <= L
 template <int N = kTok, bool FULL = false>
-__device__ __forceinline__ void load_pos(const int32_t* __restrict__ pr, int64_t l0, int64_t L,
-                                         bool pvec, int* p) {
-    if (FULL || (pvec && l0 + N <= L)) {
+__device__ __forceinline__ void load_pos(const int32_t* __restrict__ pr, int64_t l0, int64_t L, int* p) {
+    if (FULL || l0 + N <= L) {
 #pragma unroll
         for (int i = 0; i < N; i += 4) {
-            const u32x4 a = *reinterpret_cast<const u32x4*>(pr + l0 + i);
+            const u32x4 a = *reinterpret_cast<const u32x4_a4*>(pr + l0 + i);
             p[i] = (int)a.x; p[i + 1] = (int)a.y; p[i + 2] = (int)a.z; p[i + 3] = (int)a.w;
         }
     } else {
@@ -75,7 +74,7 @@ template <typename T, typename TO, int W>
 __global__ __launch_bounds__(kThreads) void conv1d_fwd_kernel(
     const T* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias,
     const int32_t* __restrict__ pos, TO* __restrict__ out, ConvStates<T, TO> st, int64_t dim,
-    int64_t L, int silu, int vec, int pvec) {
+    int64_t L, int silu) {
     const int64_t row = blockIdx.x;
     const int64_t b = row / dim, d = row - b * dim;
     const T* xr = x + row * L;
@@ -88,18 +87,18 @@ __global__ __launch_bounds__(kThreads) void conv1d_fwd_kernel(
 
     for (int64_t l0 = (int64_t)threadIdx.x * kTok; l0 < L; l0 += (int64_t)kThreads * kTok) {
         float xs[2 * kTok];
-        load_run<T, kTok>(xr, l0, L, vec, xs + kTok);
-        if (l0 > 0) load_run<T, kTok>(xr, l0 - kTok, L, vec, xs);
+        load_run<T, kTok>(xr, l0, L, xs + kTok);
+        if (l0 > 0) load_run<T, kTok>(xr, l0 - kTok, L, xs);
         else load_row_halo<T, W>(st.xinit, row, xs);
         int p[kTok];
-        load_pos(pr, l0, L, pvec, p);
+        load_pos(pr, l0, L, p);
         float o[kTok];
 #pragma unroll
         for (int i = 0; i < kTok; ++i) {
             const float v = conv_pre<W>(xs, i, p[i], wk, b0);
             o[i] = silu ? v * sigmoid_f(v) : v;
         }
-        store_run<TO, kTok>(orow, l0, L, vec, o);
+        store_run<TO, kTok>(orow, l0, L, o);
     }
     // the row's last W-1 inputs, copied as stored (reaching into xinit for short rows)
     if (st.xfinal && threadIdx.x == 0) {
@@ -128,8 +127,7 @@ template <typename T, typename TO, int W, int KT, bool DXF>
 __global__ __launch_bounds__(64) void conv1d_bwd_kernel(
     const T* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias,
     const int32_t* __restrict__ pos, const T* __restrict__ dout, TO* __restrict__ dx,
-    float* __restrict__ partial, ConvStates<T, TO> st, int64_t dim, int64_t L, int silu, int vec,
-    int pvec) {
+    float* __restrict__ partial, ConvStates<T, TO> st, int64_t dim, int64_t L, int silu) {
     static_assert(KT >= W - 1 && KT % 4 == 0, "the halo lies in the next lane's tokens");
     const int64_t row = blockIdx.x;
     const int64_t b = row / dim, d = row - b * dim;
@@ -181,20 +179,20 @@ __global__ __launch_bounds__(64) void conv1d_bwd_kernel(
             for (int k = t + 1; k < W; ++k) cgm[k][t] = k <= p ? g : 0.0f;
         }
     }
-    // One step; FULL (wave-uniform) means the step lies inside the row and vector access
-    // is allowed, so the loads and stores need no bounds checks.
+    // One step; FULL (wave-uniform) means the step lies inside the row, so the loads and
+    // stores need no bounds checks.
     auto step = [&](auto full_tag, const int64_t sidx) {
         constexpr bool FULL = decltype(full_tag)::value;
         const int64_t l0 = sidx * kSpan + (int64_t)lane * KT;
         // x of tokens l0-8 .. l0+KT-1 (pre-activations of this lane's tokens)
         float xs[kTok + KT];
-        if (l0 > 0) load_run<T, kTok, FULL>(xr, l0 - kTok, L, vec, xs);
+        if (l0 > 0) load_run<T, kTok, FULL>(xr, l0 - kTok, L, xs);
         else load_row_halo<T, W>(st.xinit, row, xs);
-        load_run<T, KT, FULL>(xr, l0, L, vec, xs + kTok);
+        load_run<T, KT, FULL>(xr, l0, L, xs + kTok);
         float gs[KT];
-        load_run<T, KT, FULL>(gr, l0, L, vec, gs);   // 0 beyond L, so g = 0 there
+        load_run<T, KT, FULL>(gr, l0, L, gs);   // 0 beyond L, so g = 0 there
         int p[KT];
-        load_pos<KT, FULL>(pr, l0, L, pvec, p);
+        load_pos<KT, FULL>(pr, l0, L, p);
         // gm[k][t] = g[t] if tap k of token t is live (k <= pos[t]) else 0, with g the
         // activation gradient.  The same masked values give dx through the reverse
         // indices (tap k of token j is live iff pos[j+k] >= k) and dw.  Tap 0 is always
@@ -245,7 +243,7 @@ __global__ __launch_bounds__(64) void conv1d_bwd_kernel(
                 if (j >= 0 && l0 + i < L) o[i] += Storage<T>::load1(st.dxfinal + row * (W - 1) + j);
             }
         }
-        store_run<TO, KT, FULL>(dxr, l0, L, vec, o);
+        store_run<TO, KT, FULL>(dxr, l0, L, o);
         // parameter gradients from this lane's own tokens
 #pragma unroll
         for (int i = 0; i < KT; ++i) {
@@ -255,7 +253,7 @@ __global__ __launch_bounds__(64) void conv1d_bwd_kernel(
         }
     };
     for (int64_t sidx = s1 - 1; sidx >= s0; --sidx) {
-        if (vec && pvec && (sidx + 1) * kSpan <= L) step(std::true_type{}, sidx);
+        if ((sidx + 1) * kSpan <= L) step(std::true_type{}, sidx);
         else step(std::false_type{}, sidx);
     }
     // gradient of the inputs before the row: initial input j (token j-W+1) meets output
@@ -300,40 +298,36 @@ __global__ void conv1d_bwd_finalize(const float* __restrict__ partial, float* __
 
 template <typename T, typename TO>
 hipError_t conv_fwd_t(const ConvArgs& a, hipStream_t s) {
-    const int vec = (a.seqlen % Storage<T>::kPerVec) == 0 && (a.seqlen % Storage<TO>::kPerVec) == 0;
-    const int pvec = (a.seqlen % 4) == 0;
     dim3 grid((unsigned)(a.batch * a.dim)), block(kThreads);
     const T* x = static_cast<const T*>(a.x);
     TO* o = static_cast<TO*>(a.out);
     const ConvStates<T, TO> st{static_cast<const T*>(a.xinit), static_cast<T*>(a.xfinal), nullptr, nullptr};
     switch (a.width) {
-        case 2: hipLaunchKernelGGL((conv1d_fwd_kernel<T, TO, 2>), grid, block, 0, s, x, a.w, a.bias, a.pos, o, st, a.dim, a.seqlen, a.silu, vec, pvec); break;
-        case 3: hipLaunchKernelGGL((conv1d_fwd_kernel<T, TO, 3>), grid, block, 0, s, x, a.w, a.bias, a.pos, o, st, a.dim, a.seqlen, a.silu, vec, pvec); break;
-        default: hipLaunchKernelGGL((conv1d_fwd_kernel<T, TO, 4>), grid, block, 0, s, x, a.w, a.bias, a.pos, o, st, a.dim, a.seqlen, a.silu, vec, pvec); break;
+        case 2: hipLaunchKernelGGL((conv1d_fwd_kernel<T, TO, 2>), grid, block, 0, s, x, a.w, a.bias, a.pos, o, st, a.dim, a.seqlen, a.silu); break;
+        case 3: hipLaunchKernelGGL((conv1d_fwd_kernel<T, TO, 3>), grid, block, 0, s, x, a.w, a.bias, a.pos, o, st, a.dim, a.seqlen, a.silu); break;
+        default: hipLaunchKernelGGL((conv1d_fwd_kernel<T, TO, 4>), grid, block, 0, s, x, a.w, a.bias, a.pos, o, st, a.dim, a.seqlen, a.silu); break;
     }
     return hipGetLastError();
 }
 
 template <typename T, typename TO, int W, bool DXF>
-void conv_bwd_w(const ConvArgs& a, hipStream_t s, int vec, int pvec) {
+void conv_bwd_w(const ConvArgs& a, hipStream_t s) {
     const ConvStates<T, TO> st{static_cast<const T*>(a.xinit), nullptr, static_cast<const T*>(a.dxfinal),
                                static_cast<TO*>(a.dxinit)};
     const unsigned nseg = (unsigned)conv_bwd_segments(a.batch, a.dim, a.seqlen);
     hipLaunchKernelGGL((conv1d_bwd_kernel<T, TO, W, kTokBwd, DXF>), dim3((unsigned)(a.batch * a.dim), nseg),
                        dim3(64), 0, s, static_cast<const T*>(a.x), a.w, a.bias, a.pos,
                        static_cast<const T*>(a.dout), static_cast<TO*>(a.out), a.partial, st, a.dim,
-                       a.seqlen, a.silu, vec, pvec);
+                       a.seqlen, a.silu);
 }
 
 template <typename T, typename TO>
 hipError_t conv_bwd_t(const ConvArgs& a, hipStream_t s) {
-    const int vec = (a.seqlen % Storage<T>::kPerVec) == 0 && (a.seqlen % Storage<TO>::kPerVec) == 0;
-    const int pvec = (a.seqlen % 4) == 0;
     const bool dxf = a.dxfinal != nullptr;
     switch (a.width) {
-        case 2: dxf ? conv_bwd_w<T, TO, 2, true>(a, s, vec, pvec) : conv_bwd_w<T, TO, 2, false>(a, s, vec, pvec); break;
-        case 3: dxf ? conv_bwd_w<T, TO, 3, true>(a, s, vec, pvec) : conv_bwd_w<T, TO, 3, false>(a, s, vec, pvec); break;
-        default: dxf ? conv_bwd_w<T, TO, 4, true>(a, s, vec, pvec) : conv_bwd_w<T, TO, 4, false>(a, s, vec, pvec); break;
+        case 2: dxf ? conv_bwd_w<T, TO, 2, true>(a, s) : conv_bwd_w<T, TO, 2, false>(a, s); break;
+        case 3: dxf ? conv_bwd_w<T, TO, 3, true>(a, s) : conv_bwd_w<T, TO, 3, false>(a, s); break;
+        default: dxf ? conv_bwd_w<T, TO, 4, true>(a, s) : conv_bwd_w<T, TO, 4, false>(a, s); break;
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

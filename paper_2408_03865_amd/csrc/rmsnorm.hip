@@ -51,7 +51,7 @@ template <typename T, typename TO>
 __global__ __launch_bounds__(kThreads) void rmsnorm_fwd_kernel(const T* __restrict__ x,
                                                                const float* __restrict__ w, float eps,
                                                                TO* __restrict__ out, float* __restrict__ rstd,
-                                                               int64_t dim, int64_t L, int vec) {
+                                                               int64_t dim, int64_t L) {
     __shared__ RmsSmem sm;
     const int tid = threadIdx.x, grp = tid & (kGroups - 1), sl = tid / kGroups;
     const int64_t b = blockIdx.y;
@@ -61,7 +61,7 @@ __global__ __launch_bounds__(kThreads) void rmsnorm_fwd_kernel(const T* __restri
     float s[kTok] = {};
     for (int64_t f = sl; f < dim; f += kSlices) {
         float v[kTok];
-        load_run<T, kTok>(xb + f * L, l0, L, vec, v);
+        load_run<T, kTok>(xb + f * L, l0, L, v);
 #pragma unroll
         for (int k = 0; k < kTok; ++k) s[k] = fmaf(v[k], v[k], s[k]);
     }
@@ -76,11 +76,11 @@ __global__ __launch_bounds__(kThreads) void rmsnorm_fwd_kernel(const T* __restri
     }
     for (int64_t f = sl; f < dim; f += kSlices) {
         float v[kTok];
-        load_run<T, kTok>(xb + f * L, l0, L, vec, v);
+        load_run<T, kTok>(xb + f * L, l0, L, v);
         const float wf = w[f];
 #pragma unroll
         for (int k = 0; k < kTok; ++k) v[k] = v[k] * r[k] * wf;
-        store_run<TO, kTok>(ob + f * L, l0, L, vec, v);
+        store_run<TO, kTok>(ob + f * L, l0, L, v);
     }
 }
 
@@ -90,7 +90,7 @@ template <typename T, typename TO>
 __global__ __launch_bounds__(kThreads) void rmsnorm_bwd_kernel(
     const T* __restrict__ x, const float* __restrict__ w, const float* __restrict__ rstd,
     const T* __restrict__ dh, const T* __restrict__ dres, TO* __restrict__ dx,
-    float* __restrict__ partial, int64_t dim, int64_t L, int vec) {
+    float* __restrict__ partial, int64_t dim, int64_t L) {
     __shared__ RmsSmem sm;
     const int tid = threadIdx.x, grp = tid & (kGroups - 1), sl = tid / kGroups;
     const int64_t b = blockIdx.y;
@@ -100,8 +100,8 @@ __global__ __launch_bounds__(kThreads) void rmsnorm_bwd_kernel(
     float s[kTok] = {};
     for (int64_t f = sl; f < dim; f += kSlices) {
         float xv[kTok], gv[kTok];
-        load_run<T, kTok>(x + off + f * L, l0, L, vec, xv);
-        load_run<T, kTok>(dh + off + f * L, l0, L, vec, gv);
+        load_run<T, kTok>(x + off + f * L, l0, L, xv);
+        load_run<T, kTok>(dh + off + f * L, l0, L, gv);
         const float wf = w[f];
 #pragma unroll
         for (int k = 0; k < kTok; ++k) s[k] = fmaf(gv[k] * wf, xv[k], s[k]);
@@ -116,9 +116,9 @@ __global__ __launch_bounds__(kThreads) void rmsnorm_bwd_kernel(
     float* pb = partial + (b * gridDim.x + tile) * dim;
     for (int64_t f = sl; f < dim; f += kSlices) {
         float xv[kTok], gv[kTok], o[kTok];
-        load_run<T, kTok>(x + off + f * L, l0, L, vec, xv);
-        load_run<T, kTok>(dh + off + f * L, l0, L, vec, gv);
-        if (dres) load_run<T, kTok>(dres + off + f * L, l0, L, vec, o);
+        load_run<T, kTok>(x + off + f * L, l0, L, xv);
+        load_run<T, kTok>(dh + off + f * L, l0, L, gv);
+        if (dres) load_run<T, kTok>(dres + off + f * L, l0, L, o);
         const float wf = w[f];
         float pw = 0.0f;
 #pragma unroll
@@ -127,7 +127,7 @@ __global__ __launch_bounds__(kThreads) void rmsnorm_bwd_kernel(
             o[k] = dres ? o[k] + v : v;
             pw = fmaf(gv[k] * xv[k], r[k], pw);      // 0 past the row end: loads read 0
         }
-        store_run<TO, kTok>(dx + off + f * L, l0, L, vec, o);
+        store_run<TO, kTok>(dx + off + f * L, l0, L, o);
         // over the 8 groups of the slice (consecutive lanes), in a fixed order
         pw += __shfl_xor(pw, 1, kGroups);
         pw += __shfl_xor(pw, 2, kGroups);
@@ -169,21 +169,19 @@ __global__ void rmsnorm_bwd_finalize(const float* __restrict__ slabs, float* __r
 
 template <typename T, typename TO>
 hipError_t fwd_t(const RmsArgs& a, hipStream_t s) {
-    const int vec = (a.seqlen % Storage<T>::kPerVec) == 0 && (a.seqlen % Storage<TO>::kPerVec) == 0;
     const dim3 grid((unsigned)((a.seqlen + kTile - 1) / kTile), (unsigned)a.batch);
     hipLaunchKernelGGL((rmsnorm_fwd_kernel<T, TO>), grid, dim3(kThreads), 0, s, static_cast<const T*>(a.x),
-                       a.w, a.eps, static_cast<TO*>(a.out), a.rstd_out, a.dim, a.seqlen, vec);
+                       a.w, a.eps, static_cast<TO*>(a.out), a.rstd_out, a.dim, a.seqlen);
     return hipGetLastError();
 }
 
 template <typename T, typename TO>
 hipError_t bwd_t(const RmsArgs& a, hipStream_t s) {
-    const int vec = (a.seqlen % Storage<T>::kPerVec) == 0 && (a.seqlen % Storage<TO>::kPerVec) == 0;
     const int64_t tiles = (a.seqlen + kTile - 1) / kTile;
     const dim3 grid((unsigned)tiles, (unsigned)a.batch);
     hipLaunchKernelGGL((rmsnorm_bwd_kernel<T, TO>), grid, dim3(kThreads), 0, s, static_cast<const T*>(a.x),
                        a.w, a.rstd, static_cast<const T*>(a.dout), static_cast<const T*>(a.dres),
-                       static_cast<TO*>(a.out), a.partial, a.dim, a.seqlen, vec);
+                       static_cast<TO*>(a.out), a.partial, a.dim, a.seqlen);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     float* slabs = a.partial + a.batch * tiles * a.dim;

@@ -84,7 +84,6 @@ struct BwdParams {
     int nchunk_states;
     int groups;
     int softplus;
-    int vec;
 };
 
 // Step and reset mask of token l of a row (the first token after a segment), or
@@ -159,8 +158,8 @@ void scan_bwd_kernel(BwdParams p) {
         sm.an[rr][n] = !row_end ? fast_exp2(fmaf(dt_next, A2n, m_next)) : (p.dhfinal ? 1.0f : 0.0f);
         sm.dA[rr][n] = 0.0f;
     }
-    // One chunk; FULL (block-uniform) means the chunk lies inside the row and vector
-    // access is allowed, so every load and store is unconditional.
+    // One chunk; FULL (block-uniform) means the chunk lies inside the row, so every load
+    // and store is unconditional.
     auto chunk = [&](auto full_tag, const int64_t c) {
         constexpr bool FULL = decltype(full_tag)::value;
         const int64_t lb = c * kCH;
@@ -188,8 +187,8 @@ void scan_bwd_kernel(BwdParams p) {
         for (int idx = tid * PV; idx < kN * kCH; idx += kThreads * PV) {
             const int n = idx / kCH, t = idx - n * kCH;
             float vb[PV], vc[PV];
-            load_run<T, PV, FULL>(Bb + (int64_t)n * L, lb + t, L, p.vec, vb);
-            load_run<T, PV, FULL>(Cb + (int64_t)n * L, lb + t, L, p.vec, vc);
+            load_run<T, PV, FULL>(Bb + (int64_t)n * L, lb + t, L, vb);
+            load_run<T, PV, FULL>(Cb + (int64_t)n * L, lb + t, L, vc);
             float* db = &sm.B[n][t / K][t % K];
             float* dc = &sm.C[n][t / K][t % K];
 #pragma unroll
@@ -217,23 +216,23 @@ void scan_bwd_kernel(BwdParams p) {
                 unpack_run(wd, dl);
                 unpack_run(wg, dyD);                          // dout for now
             } else {
-                load_run<T, K, FULL>(ur, l0, L, p.vec, uv);
-                load_run<T, K, FULL>(dr, l0, L, p.vec, dl);
-                load_run<T, K, FULL>(gr, l0, L, p.vec, dyD);
+                load_run<T, K, FULL>(ur, l0, L, uv);
+                load_run<T, K, FULL>(dr, l0, L, dl);
+                load_run<T, K, FULL>(gr, l0, L, dyD);
             }
             if (zr) {
                 // dz = dout (y + D u) d(z sigmoid(z))/dz: the forward saved every factor
                 // but dout, so dz is final here; dy = dout SiLU(z) enters the recurrence
                 float zv[K];
                 if constexpr (FULL) unpack_run(wz, zv);
-                else load_run<T, K, FULL>(zr, l0, L, p.vec, zv);
+                else load_run<T, K, FULL>(zr, l0, L, zv);
                 float fz[K] = {wf[0].x, wf[0].y, wf[0].z, wf[0].w, wf[1].x, wf[1].y, wf[1].z, wf[1].w};
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     fz[k] *= dyD[k];
                     dyD[k] *= zv[k] * sigmoid_f(zv[k]);
                 }
-                if (active) store_run<TO, K, FULL, true>(dzr, l0, L, p.vec, fz);
+                if (active) store_run<TO, K, FULL, true>(dzr, l0, L, fz);
             }
 #pragma unroll
             for (int k = 0; k < K; ++k) {
@@ -387,8 +386,8 @@ void scan_bwd_kernel(BwdParams p) {
         float o_du[K], o_dd[K];
         {
             float uv[K], dl[K];
-            load_run<T, K, FULL>(ur, l0, L, p.vec, uv);
-            load_run<T, K, FULL>(dr, l0, L, p.vec, dl);
+            load_run<T, K, FULL>(ur, l0, L, uv);
+            load_run<T, K, FULL>(dr, l0, L, dl);
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 o_du[k] = fmaf(dyD[k], Dd, dt[k] * sdhB[k]);
@@ -399,13 +398,13 @@ void scan_bwd_kernel(BwdParams p) {
             }
         }
         if (active) {
-            store_run<TO, K, FULL, true>(dur, l0, L, p.vec, o_du);
-            store_run<TO, K, FULL, true>(ddr, l0, L, p.vec, o_dd);
+            store_run<TO, K, FULL, true>(dur, l0, L, o_du);
+            store_run<TO, K, FULL, true>(ddr, l0, L, o_dd);
         }
         __syncthreads();     // LDS is restaged for the next chunk
     };
     for (int64_t c = c1 - 1; c >= c0; --c) {
-        if (p.vec && (c + 1) * kCH <= L) chunk(std::true_type{}, c);
+        if ((c + 1) * kCH <= L) chunk(std::true_type{}, c);
         else chunk(std::false_type{}, c);
     }
 
@@ -487,7 +486,7 @@ __global__ __launch_bounds__(kThreads) void scan_bwd_agg_kernel(BwdParams p) {
         for (int idx = tid * PV; idx < kN * kCH; idx += kThreads * PV) {
             const int n = idx / kCH, t = idx - n * kCH;
             float vc[PV];
-            load_run<T, PV, FULL>(Cb + (int64_t)n * L, lb + t, L, p.vec, vc);
+            load_run<T, PV, FULL>(Cb + (int64_t)n * L, lb + t, L, vc);
             float* dc = &sm.C[n][t / K][t % K];
 #pragma unroll
             for (int i = 0; i < PV; ++i) dc[i] = vc[i];
@@ -503,11 +502,11 @@ __global__ __launch_bounds__(kThreads) void scan_bwd_agg_kernel(BwdParams p) {
         float S = 0.0f, Mr = 0.0f;
         {
             float dl[K];
-            load_run<T, K, FULL>(dr, l0, L, p.vec, dl);
-            load_run<T, K, FULL>(gr, l0, L, p.vec, dyD);
+            load_run<T, K, FULL>(dr, l0, L, dl);
+            load_run<T, K, FULL>(gr, l0, L, dyD);
             if (zr) {
                 float zv[K];
-                load_run<T, K, FULL>(zr, l0, L, p.vec, zv);
+                load_run<T, K, FULL>(zr, l0, L, zv);
 #pragma unroll
                 for (int k = 0; k < K; ++k) dyD[k] *= zv[k] * sigmoid_f(zv[k]);
             }
@@ -570,7 +569,7 @@ __global__ __launch_bounds__(kThreads) void scan_bwd_agg_kernel(BwdParams p) {
     // token before a sequence start, or underflow of a long decay), the later chunks
     // contribute exactly nothing, and the walk stops.
     for (int64_t c = c0; c < c1; ++c) {
-        if (p.vec && (c + 1) * kCH <= L) chunk(std::true_type{}, c);
+        if ((c + 1) * kCH <= L) chunk(std::true_type{}, c);
         else chunk(std::false_type{}, c);
         if (!__syncthreads_or(sm.q[tid >> 4][tid & 15] != 0.0f)) break;
     }
@@ -659,7 +658,6 @@ hipError_t launch_t(const ScanArgs& a, hipStream_t s) {
     p.nchunk_states = (int)((a.seqlen + kCH - 1) / kCH);
     p.groups = (int)((a.dim + kRows - 1) / kRows);
     p.softplus = a.softplus;
-    p.vec = (a.seqlen % Storage<T>::kPerVec) == 0 && (a.seqlen % Storage<TO>::kPerVec) == 0;
     const SegPlan sp = scan_segments(a.batch, a.dim, a.seqlen, kSegTargetBwd);
     static_assert(kSegUnit % kCH == 0, "segments hold whole chunks");
     p.seg_chunks = sp.seg_len / kCH;

@@ -72,7 +72,6 @@ struct FwdParams {
     int nseg;
     int nchunk_states;
     int softplus;
-    int vec;
 };
 
 // AGG: aggregate pass over one segment (no C, no outputs), writes its map (P, H).
@@ -118,8 +117,8 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
     const float dbias = p.delta_bias ? p.delta_bias[d] : 0.0f;
 
     const int64_t nchunk = (L + CH - 1) / CH;
-    // One chunk; FULL (block-uniform) means the chunk lies inside the row and vector
-    // access is allowed, so every load and store is unconditional.
+    // One chunk; FULL (block-uniform) means the chunk lies inside the row, so every load
+    // and store is unconditional.
     auto chunk = [&](auto full_tag, const int64_t c) {
         constexpr bool FULL = decltype(full_tag)::value;
         const int64_t lb = c * CH;
@@ -135,8 +134,8 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
         for (int idx = tid * PV; idx < kN * CH; idx += kThreads * PV) {
             const int n = idx / CH, t = idx - n * CH;
             float vb[PV], vc[PV];
-            load_run<T, PV, FULL>(Bb + (int64_t)n * L, lb + t, L, p.vec, vb);
-            if (!AGG) load_run<T, PV, FULL>(Cb + (int64_t)n * L, lb + t, L, p.vec, vc);
+            load_run<T, PV, FULL>(Bb + (int64_t)n * L, lb + t, L, vb);
+            if (!AGG) load_run<T, PV, FULL>(Cb + (int64_t)n * L, lb + t, L, vc);
             float* db = &sm.B[n][t / K][t % K];
             float* dc = &sm.C[n][t / K][t % K];
 #pragma unroll
@@ -159,8 +158,8 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
                 unpack_run(wu, uv);
                 unpack_run(wd, dt);
             } else {
-                load_run<T, K, FULL>(ur, l0, L, p.vec, uv);
-                load_run<T, K, FULL>(dr, l0, L, p.vec, dt);
+                load_run<T, K, FULL>(ur, l0, L, uv);
+                load_run<T, K, FULL>(dr, l0, L, dt);
             }
 #pragma unroll
             for (int k = 0; k < K; ++k) {
@@ -242,7 +241,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
         if (!AGG && active && (orow || p.dzf)) {
             if (zr) {
                 float zv[K], g[K];
-                load_run<T, K, FULL>(zr, l0, L, p.vec, zv);
+                load_run<T, K, FULL>(zr, l0, L, zv);
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     const float sz = sigmoid_f(zv[k]);
@@ -258,7 +257,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
                                                     reinterpret_cast<f32x4*>(fr + dzf_vec(c, i, j)));
                 }
             }
-            if (orow) store_run<TO, K, FULL>(orow, l0, L, p.vec, y);
+            if (orow) store_run<TO, K, FULL>(orow, l0, L, y);
         }
         __syncthreads();      // LDS is restaged for the next chunk
     };
@@ -270,13 +269,13 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
         // block (a sequence start, or underflow of a long decay), the earlier chunks
         // contribute exactly nothing, and the walk stops.
         for (int64_t c = c1 - 1; c >= c0; --c) {
-            if (p.vec && (c + 1) * CH <= L) chunk(std::true_type{}, c);
+            if ((c + 1) * CH <= L) chunk(std::true_type{}, c);
             else chunk(std::false_type{}, c);
             if (!__syncthreads_or(sm.pseg[tid >> 4][tid & 15] != 0.0f)) break;
         }
     } else {
         for (int64_t c = c0; c < c1; ++c) {
-            if (p.vec && (c + 1) * CH <= L) chunk(std::true_type{}, c);
+            if ((c + 1) * CH <= L) chunk(std::true_type{}, c);
             else chunk(std::false_type{}, c);
         }
     }
@@ -325,7 +324,6 @@ hipError_t launch_t(const ScanArgs& a, hipStream_t s) {
     p.dim = a.dim; p.L = a.seqlen;
     p.nchunk_states = (int)((a.seqlen + kStride - 1) / kStride);
     p.softplus = a.softplus;
-    p.vec = (a.seqlen % Storage<T>::kPerVec) == 0 && (a.seqlen % Storage<TO>::kPerVec) == 0;
     const SegPlan sp = scan_segments(a.batch, a.dim, a.seqlen, kSegTargetFwd);
     static_assert(kSegUnit % (16 * K) == 0, "segments hold whole chunks");
     p.seg_chunks = sp.seg_len / (16 * K);
