@@ -160,8 +160,11 @@ __device__ __forceinline__ void store_run(T* __restrict__ row, int64_t l0, int64
 // outside its row keeps `old`)
 // ---------------------------------------------------------------------------
 enum : int {
+    kQuadXor1 = 0xb1,           // quad_perm:[1,0,3,2]
+    kQuadXor2 = 0x4e,           // quad_perm:[2,3,0,1]
     kRowShl1 = 0x101,
     kRowShr1 = 0x111,
+    kWaveShr1 = 0x138,
     kNewBcast0 = 0x150,
     kNewBcast15 = 0x15f,
 };

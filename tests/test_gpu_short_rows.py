@@ -1,0 +1,84 @@
+"""GPU parity of the paths whose launch depends on the row length: the scan forward's short-row
+kernel (no saved states, up to 32 tokens) on both sides of its limit, and the conv forward's
+lanes per row, tiles per row and rows per lane, against the oracle."""
+import numpy as np
+import pytest
+
+import workloads as W
+from gpu_common import TOL, act, assert_close, f32, host, i32, note
+
+pytestmark = pytest.mark.gpu
+
+
+def _cfg(batch, dim, seqlen, width, dtype):
+    return W.Config("short", "short", batch, seqlen, dim, 16, width, dtype, ("lognormal", 1.5, 1.0, 1, max(seqlen, 1)),
+                    8800 + batch * 13 + dim * 3 + seqlen)
+
+
+# tokens: one vector and less, the limit of the short kernel and one token on either side;
+# channels: one, a block of 64 and one on either side
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("states", [False, True], ids=["fresh", "continued"])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (3, 65, 1), (2, 64, 2), (2, 63, 7), (1, 130, 31), (2, 40, 32), (2, 40, 33)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_scan_forward_short_rows(shape, states, dtype):
+    import oracle as O
+    import paper_2408_03865_amd as P
+    batch, dim, L = shape
+    d = W.make_inputs(_cfg(batch, dim, L, 4, dtype), variant="general")
+    pos, h0 = d["pos"].copy(), None
+    if states:
+        first = np.argmax(np.concatenate([pos[:, 1:] == 0, np.ones((batch, 1), bool)], 1), 1) + 1
+        for b in range(batch):
+            pos[b, :first[b]] += 5
+        h0 = np.random.default_rng(L).standard_normal((batch, dim, 16)).astype(np.float32)
+    note(f"short scan {shape} {dtype} states={states}")
+    g = {k: act(d[k], dtype) for k in ("u", "delta", "B", "C", "z")}
+    par = {k: f32(d[k]) for k in ("A", "D", "delta_bias")}
+    for opts in (dict(D=True, z=True, bias=True, softplus=True), dict(D=False, z=False, bias=False, softplus=False)):
+        got, fin = P.selective_scan_fwd(g["u"], g["delta"], par["A"], g["B"], g["C"], par["D"] if opts["D"] else None,
+                                        g["z"] if opts["z"] else None, par["delta_bias"] if opts["bias"] else None,
+                                        opts["softplus"], i32(pos), out_f32=dtype == "bf16", initial_state=f32(h0),
+                                        return_final=True)
+        ref, rfin = O.scan_fwd(u=d["u"], delta=d["delta"], A=d["A"], B=d["B"], C=d["C"],
+                               D=d["D"] if opts["D"] else None, z=d["z"] if opts["z"] else None,
+                               delta_bias=d["delta_bias"] if opts["bias"] else None, delta_softplus=opts["softplus"],
+                               pos=pos, h0=h0, return_final=True)
+        assert_close("out", host(got), ref, TOL["f32"])        # same inputs and fp32 arithmetic for both types
+        assert_close("final", host(fin), rfin, TOL["f32"])
+
+
+# tokens around one lane's vector (4 and 8), around the powers of two of lanes per row, a wave's
+# span (256 and 512) and more tiles; channels that leave a wave's rows ragged.  The last shapes
+# have enough rows for four per lane: 64 rows a wave, and one row in two tiles.
+CONV_SHAPES = [(1, 1, 1), (2, 70, 2), (3, 33, 5), (2, 5, 8), (2, 17, 9), (1, 9, 31), (2, 3, 255), (1, 6, 257),
+               (2, 3, 512), (1, 5, 513), (1, 2, 1541), (64, 33000, 1), (130, 131, 513)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("width", [2, 3, 4])
+@pytest.mark.parametrize("shape", CONV_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_conv_forward_lanes_and_tiles(shape, width, dtype):
+    import oracle as O
+    import paper_2408_03865_amd as P
+    batch, dim, L = shape
+    if batch * dim * L > 1 << 20 and width != 4:
+        pytest.skip("the large shapes run at one width")
+    rng = np.random.default_rng(batch + dim + L + width)
+    rnd = W.bf16_round if dtype == "bf16" else (lambda a: a)
+    x = rnd(rng.standard_normal((batch, dim, L)).astype(np.float32))
+    xi = rnd(rng.standard_normal((batch, dim, width - 1)).astype(np.float32))
+    w = rng.uniform(-0.5, 0.5, (dim, width)).astype(np.float32)
+    bias = rng.uniform(-0.5, 0.5, dim).astype(np.float32)
+    pos = W.positions_from_lengths(W.draw_row_lengths(("lognormal", 4.0, 2.0, 1, L), rng, batch, L), L)
+    first = np.argmax(np.concatenate([pos[:, 1:] == 0, np.ones((batch, 1), bool)], 1), 1) + 1
+    for b in range(0, batch, 2):                       # every other row continues a sequence
+        pos[b, :first[b]] += 1 + b % 4
+    note(f"conv {shape} W={width} {dtype}")
+    got, fin = P.causal_conv1d_fwd(act(x, dtype), f32(w), f32(bias), i32(pos), out_f32=dtype == "bf16",
+                                   initial_x=act(xi, dtype), return_final=True)
+    ref, rfin = O.conv1d_fwd(x, w, bias, pos, xinit=xi, return_final=True)
+    assert_close("out", host(got), ref, TOL["f32"])
+    assert np.array_equal(host(fin), np.asarray(rfin, dtype=np.float64))
+    plain = P.causal_conv1d_fwd(act(x, dtype), f32(w), None, i32(pos), silu=False, out_f32=dtype == "bf16")
+    assert_close("plain", host(plain), O.conv1d_fwd(x, w, None, pos, silu=False), TOL["f32"])
