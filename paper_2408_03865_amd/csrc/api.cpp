@@ -37,26 +37,13 @@ int64_t state_chunks(int64_t seqlen) {
 }
 
 // Segment split workspace, shared by both directions: the per-segment maps
-// (batch, dim, nseg, kN, 2) followed by the chained carries (batch, dim, nseg, kN).
-// Empty when the rows are not split.
-struct SegWs {
-    size_t agg, carry, total;
-};
-
-SegWs seg_ws(int64_t batch, int64_t dim, int64_t seqlen, int64_t target) {
+// (batch, dim, nseg, kN, 2), and a third float for each that no kernel uses: the size that
+// callers were told stays what it was when the chained carries were stored.  Empty when
+// the rows are not split.
+size_t seg_ws(int64_t batch, int64_t dim, int64_t seqlen, int64_t target) {
     const pm::SegPlan sp = pm::scan_segments(batch, dim, seqlen, target);
-    SegWs w{0, 0, 0};
-    if (sp.nseg > 1) {
-        w.agg = align_up(sizeof(float) * (size_t)(batch * dim * sp.nseg * kN * 2));
-        w.carry = align_up(sizeof(float) * (size_t)(batch * dim * sp.nseg * kN));
-        w.total = w.agg + w.carry;
-    }
-    return w;
-}
-
-void set_seg_ws(pm::ScanArgs& a, char* base, const SegWs& w) {
-    a.ws_agg = w.total ? reinterpret_cast<float*>(base) : nullptr;
-    a.ws_carry = w.total ? reinterpret_cast<float*>(base + w.agg) : nullptr;
+    const size_t maps = sizeof(float) * (size_t)(batch * dim * sp.nseg * kN);
+    return sp.nseg > 1 ? align_up(2 * maps) + align_up(maps) : 0;
 }
 
 // Saved states of the forward: the chunk states (batch, dim, chunk, dstate), then the
@@ -78,7 +65,6 @@ SavedLayout saved_layout(int64_t batch, int64_t dim, int64_t seqlen) {
 // (used when none are passed), then the segment workspace.
 struct ScanWs {
     size_t part_bc, part_chan, states, total;
-    SegWs seg;
 };
 
 ScanWs scan_ws(int64_t batch, int64_t dim, int64_t seqlen) {
@@ -88,8 +74,8 @@ ScanWs scan_ws(int64_t batch, int64_t dim, int64_t seqlen) {
     w.part_bc = align_up(sizeof(float) * (size_t)(batch * groups * 2 * kN * seqlen));
     w.part_chan = align_up(sizeof(float) * (size_t)(batch * nseg * dim * (kN + 2)));
     w.states = saved_layout(batch, dim, seqlen).total;
-    w.seg = seg_ws(batch, dim, seqlen, pm::kSegTargetBwd);   // covers the forward's plan too
-    w.total = w.part_bc + w.part_chan + w.states + w.seg.total;
+    w.total = w.part_bc + w.part_chan + w.states +
+              seg_ws(batch, dim, seqlen, pm::kSegTargetBwd);   // covers the forward's plan too
     return w;
 }
 
@@ -206,7 +192,7 @@ size_t packmamba_selective_scan_fwd_saved_states_size(int64_t batch, int64_t dim
 size_t packmamba_selective_scan_fwd_workspace_size(int64_t batch, int64_t dim, int64_t seqlen,
                                                    int32_t dstate) {
     if (check_shape(batch, dim, seqlen) || dstate != kN) return 0;
-    return seg_ws(batch, dim, seqlen, pm::kSegTargetFwd).total;
+    return seg_ws(batch, dim, seqlen, pm::kSegTargetFwd);
 }
 
 int packmamba_selective_scan_fwd(const void* u, const void* delta, const float* A, const void* B,
@@ -227,10 +213,10 @@ int packmamba_selective_scan_fwd(const void* u, const void* delta, const float* 
         !aligned16(position_indices) || !aligned16(out) || !aligned16(saved_states) ||
         !aligned16(workspace) || !aligned16(initial_state) || !aligned16(final_state))
         return PACKMAMBA_ERR_ALIGN;
-    const SegWs w = seg_ws(batch, dim, seqlen, pm::kSegTargetFwd);
-    if (w.total && (!workspace || workspace_bytes < w.total)) return PACKMAMBA_ERR_WORKSPACE;
+    const size_t need = seg_ws(batch, dim, seqlen, pm::kSegTargetFwd);
+    if (need && (!workspace || workspace_bytes < need)) return PACKMAMBA_ERR_WORKSPACE;
     pm::ScanArgs a{};
-    set_seg_ws(a, static_cast<char*>(workspace), w);
+    a.ws_agg = static_cast<float*>(workspace);
     a.u = u; a.delta = delta; a.A = A; a.B = B; a.C = C; a.D = D; a.z = z;
     a.delta_bias = delta_bias; a.pos = position_indices; a.softplus = delta_softplus ? 1 : 0;
     a.out = out; a.states = saved_states; a.h0 = initial_state; a.hfinal = final_state;
@@ -283,7 +269,7 @@ int packmamba_selective_scan_bwd(const void* u, const void* delta, const float* 
     hipStream_t s = (hipStream_t)stream;
     // the forward recompute below and the backward run one after the other on the
     // stream, so they share the segment workspace
-    set_seg_ws(a, ws + w.part_bc + w.part_chan + w.states, w.seg);
+    a.ws_agg = reinterpret_cast<float*>(ws + w.part_bc + w.part_chan + w.states);
     char* saved = saved_states ? reinterpret_cast<char*>(const_cast<float*>(saved_states))
                                : ws + w.part_bc + w.part_chan;
     a.states = reinterpret_cast<float*>(saved);

@@ -235,14 +235,17 @@ __device__ __forceinline__ void row_scan_down(float& P, float& H) {
 // Both scans at once: the forward scan of (P, H) and the reverse scan of (Pr, Hr),
 // interleaved so that every DPP read comes at least three instructions after the
 // write of its source.  No wait states are needed inside, and each chain hides
-// the other's DPP latency.
+// the other's DPP latency.  Only H and Hr are wanted: the last step's products are left out.
 #define PM_UD_LEVEL(N)                                                        \
     "v_fmac_f32_dpp %1, %1, %0 row_shr:" #N " row_mask:0xf bank_mask:0xf\n\t" \
     "v_fmac_f32_dpp %3, %3, %2 row_shl:" #N " row_mask:0xf bank_mask:0xf\n\t" \
     "v_mul_f32_dpp %0, %0, %0 row_shr:" #N " row_mask:0xf bank_mask:0xf\n\t"  \
     "v_mul_f32_dpp %2, %2, %2 row_shl:" #N " row_mask:0xf bank_mask:0xf\n\t"
-__device__ __forceinline__ void row_scan_up_down(float& P, float& H, float& Pr, float& Hr) {
-    asm("s_nop 1\n\t" PM_UD_LEVEL(1) PM_UD_LEVEL(2) PM_UD_LEVEL(4) PM_UD_LEVEL(8) "s_nop 1"
+__device__ __forceinline__ void row_scan_up_down(float P, float& H, float Pr, float& Hr) {
+    asm("s_nop 1\n\t" PM_UD_LEVEL(1) PM_UD_LEVEL(2) PM_UD_LEVEL(4)
+        "v_fmac_f32_dpp %1, %1, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %3, %2 row_shl:8 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1"
         : "+v"(P), "+v"(H), "+v"(Pr), "+v"(Hr));
 }
 #undef PM_UD_LEVEL
@@ -251,6 +254,25 @@ __device__ __forceinline__ void row_scan_up_down(float& P, float& H, float& Pr, 
 __device__ __forceinline__ float row_sum_to_15(float x) {
     add_shr1(x); add_shr2(x); add_shr4(x); add_shr8(x);
     dpp_tail_nop(x);
+    return x;
+}
+
+// Sums over the 16 lanes of a row of two values at once: x's in lane 7, y's in lane 15.
+// The first step adds the halves of each and puts y's into lanes 8..15 of x (bank_mask
+// selects groups of four lanes), the others sum within the halves: 5 adds instead of 8.
+__device__ __forceinline__ float row_sum2_to_7_15(float x, float y) {
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_shl:8 row_mask:0xf bank_mask:0x3\n\t"      // lanes 0-7: x[j] + x[j+8]
+        "v_add_f32_dpp %0, %1, %1 row_shr:8 row_mask:0xf bank_mask:0xc\n\t"      // lanes 8-15: y[j] + y[j-8]
+        "s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t" // lane + mirrored lane of its 8
+        "s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1"
+        : "+v"(x)
+        : "v"(y));
     return x;
 }
 

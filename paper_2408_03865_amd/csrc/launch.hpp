@@ -110,9 +110,8 @@ struct ScanArgs {
     float* ddelta_bias;
     float* part_bc;         // (batch, groups, 2, dstate, seqlen)
     float* part_chan;       // (batch, nseg, dim, dstate + 2)
-    // segment split (both directions): per-segment maps and the chained carries
+    // segment split (both directions): per-segment maps
     float* ws_agg;          // (batch, dim, nseg, dstate, 2)
-    float* ws_carry;        // (batch, dim, nseg, dstate)
     int64_t batch, dim, seqlen;
     int32_t dstate, dtype;
 };
@@ -138,8 +137,7 @@ __host__ __device__ constexpr int64_t dzf_vec(int64_t c, int i, int j) {
 constexpr int kScanBwdChannels = 16;
 
 // Split of the rows into segments along the sequence, each scanned by its own
-// block with the carry across segments resolved by an aggregate pass and a carry
-// pass.  Used only when batch x (channel groups of 16) leaves the GPU underfilled:
+// block with the carry across segments resolved by an aggregate pass.  Used only when batch x (channel groups of 16) leaves the GPU underfilled:
 // 256 CUs hold three scan blocks each.  A direction splits when its blocks fill less
 // than half of its target and then aims at the target: one round of blocks (768) for
 // the forward, two (1536) for the backward, each direction's fastest (4 rows x 2048

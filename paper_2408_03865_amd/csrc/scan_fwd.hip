@@ -24,8 +24,8 @@
 //    the backward does not rebuild y.
 //  - Long rows with few channels are split into segments scanned by different
 //    blocks: an aggregate pass folds each segment into one map h -> P h + H per
-//    (channel, state), a carry pass chains the maps along the row, and the main
-//    pass starts each segment from its chained carry.
+//    (channel, state), and the main pass chains the maps before its segment and
+//    starts from that state.
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -65,14 +65,33 @@ struct FwdParams {
     float* dzf;               // (batch, dim, L): factor of dout in dz, or null
     const float* h0;          // state before each row (batch, dim, kN), or null
     float* hfinal;            // state after each row (batch, dim, kN), or null
-    float* agg;               // aggregate pass output: (batch, dim, nseg, kN, 2) = (P, H)
-    const float* carry_in;    // main pass: state before each segment (batch, dim, nseg, kN), or null
+    float2* agg;              // the segments' maps (batch, dim, nseg, kN) = (P, H): written by the
+                              // aggregate pass, chained by the main pass
     int64_t dim, L;
     int64_t seg_chunks;       // chunks per segment
     int nseg;
     int nchunk_states;
     int softplus;
 };
+
+// The state before segment `seg`: the maps h -> P h + H of the segments before it applied
+// to h, the row's initial state.  Each block chains its own: a few loads that do not wait
+// for one another, against a launch of its own for a carry pass (5 us).
+__device__ __forceinline__ float chain_maps(const float2* __restrict__ maps, int seg, float h) {
+    int s = 0;
+    for (; s + 8 <= seg; s += 8) {
+        float2 m[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) m[i] = maps[(int64_t)(s + i) * kN];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) h = fmaf(m[i].x, h, m[i].y);
+    }
+    for (; s < seg; ++s) {
+        const float2 m = maps[(int64_t)s * kN];
+        h = fmaf(m.x, h, m.y);
+    }
+    return h;
+}
 
 // AGG: aggregate pass over one segment (no C, no outputs), writes its map (P, H).
 template <typename T, typename TO, int K, bool AGG>
@@ -107,8 +126,8 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
         sm.A2[rr][n] = p.A[dd * kN + n] * kLog2e;
         float c0v = 0.0f;
         if (!AGG) {
-            if (p.carry_in) c0v = p.carry_in[((b * p.dim + dd) * p.nseg + seg) * kN + n];
-            else if (p.h0) c0v = p.h0[(b * p.dim + dd) * kN + n];
+            if (p.h0) c0v = p.h0[(b * p.dim + dd) * kN + n];
+            c0v = chain_maps(p.agg + (b * p.dim + dd) * p.nseg * kN + n, seg, c0v);
         }
         sm.carry[rr][n] = c0v;
         sm.pseg[rr][n] = 1.0f;
@@ -284,9 +303,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
         const int rr = tid >> 4, n = tid & 15;
         const int64_t dd = (int64_t)blockIdx.x * kRows + rr;
         if (dd < p.dim) {
-            float* o = p.agg + (((b * p.dim + dd) * p.nseg + seg) * kN + n) * 2;
-            o[0] = sm.pseg[rr][n];
-            o[1] = sm.carry[rr][n];
+            p.agg[((b * p.dim + dd) * p.nseg + seg) * kN + n] = float2{sm.pseg[rr][n], sm.carry[rr][n]};
         }
     } else if (p.hfinal && c1 == nchunk) {
         // the carry after the row's last chunk is h after its last token (tokens past
@@ -294,22 +311,6 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
         const int rr = tid >> 4, n = tid & 15;
         const int64_t dd = (int64_t)blockIdx.x * kRows + rr;
         if (dd < p.dim) p.hfinal[(b * p.dim + dd) * kN + n] = sm.carry[rr][n];
-    }
-}
-
-// Chains the segment maps along each row: carry[s] = state after segment s-1 (the
-// row's initial state, or 0, for s = 0).
-__global__ void scan_fwd_carry_kernel(const float* __restrict__ agg, float* __restrict__ carry,
-                                      const float* __restrict__ h0, int64_t rows_n, int nseg) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;   // over batch*dim*kN
-    if (i >= rows_n) return;
-    const int64_t bd = i / kN;
-    const int n = (int)(i - bd * kN);
-    float h = h0 ? h0[i] : 0.0f;
-    for (int s = 0; s < nseg; ++s) {
-        const int64_t o = (bd * nseg + s) * kN + n;
-        carry[o] = h;
-        if (s + 1 < nseg) h = fmaf(agg[2 * o], h, agg[2 * o + 1]);
     }
 }
 
@@ -405,21 +406,13 @@ hipError_t launch_t(const ScanArgs& a, hipStream_t s) {
     static_assert(kSegUnit % (16 * K) == 0, "segments hold whole chunks");
     p.seg_chunks = sp.seg_len / (16 * K);
     p.nseg = (int)sp.nseg;
-    p.agg = a.ws_agg;
-    p.carry_in = nullptr;
+    p.agg = reinterpret_cast<float2*>(a.ws_agg);
     const unsigned groups = (unsigned)((a.dim + kRows - 1) / kRows);
     if (sp.nseg > 1) {
-        // aggregate every segment but the last, then chain
+        // aggregate every segment but the last
         hipLaunchKernelGGL((scan_fwd_kernel<T, TO, K, true>), dim3(groups, (unsigned)a.batch, (unsigned)(sp.nseg - 1)),
                            dim3(kThreads), 0, s, p);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        const int64_t rows_n = a.batch * a.dim * kN;
-        hipLaunchKernelGGL(scan_fwd_carry_kernel, dim3((unsigned)((rows_n + 255) / 256)), dim3(256), 0, s,
-                           a.ws_agg, a.ws_carry, a.h0, rows_n, p.nseg);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        p.carry_in = a.ws_carry;
+        if (hipError_t e = hipGetLastError()) return e;
     }
     hipLaunchKernelGGL((scan_fwd_kernel<T, TO, K, false>), dim3(groups, (unsigned)a.batch, (unsigned)sp.nseg),
                        dim3(kThreads), 0, s, p);

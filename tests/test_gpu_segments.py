@@ -1,0 +1,42 @@
+"""GPU parity of rows cut into many segments, whose maps every block chains by itself in runs of
+eight: segment counts around those runs, in both directions, with initial and final states."""
+import numpy as np
+import pytest
+
+import workloads as W
+from gpu_common import TOL, act, assert_close, f32, host, i32, note
+
+pytestmark = pytest.mark.gpu
+
+
+# one sequence per row, slow decay: every map matters.  dim 16 gives as many segments as
+# the row has 256-token units: 7, 8, 9, 17 (the last one token long)
+@pytest.mark.parametrize("L", [1790, 2048, 2100, 4097])
+def test_segment_chains(L):
+    import oracle as O
+    import paper_2408_03865_amd as P
+    batch, dim = 2, 16
+    assert P.segments(batch, dim, L, "fwd") == P.segments(batch, dim, L, "bwd") == (L + 255) // 256
+    cfg = W.Config("chain", "chain", batch, L, dim, 16, 4, "f32", ("arange",), 7700 + L)
+    d = W.make_inputs(cfg, variant="general")
+    A = d["A"] * np.float32(0.02)
+    rng = np.random.default_rng(L)
+    h0, dhf = (rng.standard_normal((batch, dim, 16)).astype(np.float32) for _ in range(2))
+    pos = d["pos"] + 3                                  # the rows continue sequences: no reset at all
+    note(f"chain L={L}")
+    g = {k: act(d[k], "f32") for k in ("u", "delta", "B", "C", "z", "dout")}
+    a = (g["u"], g["delta"], f32(A), g["B"], g["C"], f32(d["D"]), g["z"], f32(d["delta_bias"]), True, i32(pos))
+    y, st, fin = P.selective_scan_fwd(*a, return_states=True, initial_state=f32(h0), return_final=True)
+    gr = P.selective_scan_bwd(*a, g["dout"], saved_states=st, initial_state=f32(h0), dfinal_state=f32(dhf))
+    args = dict(u=d["u"], delta=d["delta"], A=A, B=d["B"], C=d["C"], D=d["D"], z=d["z"], delta_bias=d["delta_bias"],
+                delta_softplus=True, pos=pos)
+    ry, rfin = O.scan_fwd(**args, h0=h0, return_final=True)
+    ref = O.scan_bwd(**args, dout=d["dout"], h0=h0, dhfinal=dhf)
+    # sums of up to L terms of either sign: an ulp of the largest value stands beside the bound
+    for k, got, want in [("out", y, ry), ("final", fin, rfin), ("du", gr["du"], ref["du"]), ("ddelta", gr["ddelta"], ref["ddelta"]),
+                         ("dA", gr["dA"], ref["dA"]), ("dB", gr["dB"], ref["dB"]), ("dC", gr["dC"], ref["dC"]),
+                         ("dh0", gr["dinitial_state"], ref["dh0"])]:
+        want = np.asarray(want, dtype=np.float64)
+        floor = 16 * 2.0 ** -24 * np.max(np.abs(want))
+        err = np.abs(host(got) - want)
+        assert np.all(err <= TOL["f32"] * (1 + np.abs(want)) + floor), f"{k}: {err.max():.3e}"
