@@ -145,7 +145,7 @@ def segments(batch: int, dim: int, seqlen: int, direction: str = "bwd") -> int:
     target = {"fwd": 768, "bwd": 1536}[direction]
     blocks = batch * ((dim + 15) // 16)
     units = (seqlen + 255) // 256
-    if blocks * 2 >= target or units < 2:
+    if blocks * 2 >= target or units < 2 or (direction == "fwd" and blocks >= 256 and seqlen <= 4096):
         return 1
     nseg = min((target + blocks - 1) // blocks, units)
     per = (units + nseg - 1) // nseg

@@ -40,8 +40,7 @@ int64_t state_chunks(int64_t seqlen) {
 // (batch, dim, nseg, kN, 2), and a third float for each that no kernel uses: the size that
 // callers were told stays what it was when the chained carries were stored.  Empty when
 // the rows are not split.
-size_t seg_ws(int64_t batch, int64_t dim, int64_t seqlen, int64_t target) {
-    const pm::SegPlan sp = pm::scan_segments(batch, dim, seqlen, target);
+size_t seg_ws(int64_t batch, int64_t dim, const pm::SegPlan& sp) {
     const size_t maps = sizeof(float) * (size_t)(batch * dim * sp.nseg * kN);
     return sp.nseg > 1 ? align_up(2 * maps) + align_up(maps) : 0;
 }
@@ -75,7 +74,7 @@ ScanWs scan_ws(int64_t batch, int64_t dim, int64_t seqlen) {
     w.part_chan = align_up(sizeof(float) * (size_t)(batch * nseg * dim * (kN + 2)));
     w.states = saved_layout(batch, dim, seqlen).total;
     w.total = w.part_bc + w.part_chan + w.states +
-              seg_ws(batch, dim, seqlen, pm::kSegTargetBwd);   // covers the forward's plan too
+              seg_ws(batch, dim, pm::scan_segments(batch, dim, seqlen, pm::kSegTargetBwd));   // covers the forward's plan too
     return w;
 }
 
@@ -192,7 +191,7 @@ size_t packmamba_selective_scan_fwd_saved_states_size(int64_t batch, int64_t dim
 size_t packmamba_selective_scan_fwd_workspace_size(int64_t batch, int64_t dim, int64_t seqlen,
                                                    int32_t dstate) {
     if (check_shape(batch, dim, seqlen) || dstate != kN) return 0;
-    return seg_ws(batch, dim, seqlen, pm::kSegTargetFwd);
+    return seg_ws(batch, dim, pm::scan_fwd_plan(batch, dim, seqlen).seg);
 }
 
 int packmamba_selective_scan_fwd(const void* u, const void* delta, const float* A, const void* B,
@@ -213,7 +212,7 @@ int packmamba_selective_scan_fwd(const void* u, const void* delta, const float* 
         !aligned16(position_indices) || !aligned16(out) || !aligned16(saved_states) ||
         !aligned16(workspace) || !aligned16(initial_state) || !aligned16(final_state))
         return PACKMAMBA_ERR_ALIGN;
-    const size_t need = seg_ws(batch, dim, seqlen, pm::kSegTargetFwd);
+    const size_t need = seg_ws(batch, dim, pm::scan_fwd_plan(batch, dim, seqlen).seg);
     if (need && (!workspace || workspace_bytes < need)) return PACKMAMBA_ERR_WORKSPACE;
     pm::ScanArgs a{};
     a.ws_agg = static_cast<float*>(workspace);

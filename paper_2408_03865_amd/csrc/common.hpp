@@ -25,6 +25,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // instruction (the HSA runtime runs in unaligned access mode), so a row whose length is
 // no multiple of the vector, and with it every row but the first, takes the same code as
 // an aligned one.
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
+typedef u32x2 u32x2_a4 __attribute__((aligned(4)));
 typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
 typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
 typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
@@ -43,6 +46,7 @@ template <typename T> struct Storage;
 
 template <> struct Storage<float> {
     typedef u32x4_a4 Vec;
+    typedef u32x2_a4 Half;
     static constexpr int kBytes = 4;
     static constexpr int kPerVec = 4;     // elements per 16-byte vector
     __device__ static float load1(const float* p) { return *p; }
@@ -60,6 +64,7 @@ template <> struct Storage<float> {
 
 template <> struct Storage<bf16_t> {
     typedef u32x4_a2 Vec;
+    typedef u32x2_a2 Half;
     static constexpr int kBytes = 2;
     static constexpr int kPerVec = 8;
     __device__ static float load1(const bf16_t* p) { return __uint_as_float((uint32_t)p->bits << 16); }
@@ -77,6 +82,48 @@ template <> struct Storage<bf16_t> {
     }
 };
 
+// K consecutive elements at row[l0] as raw vectors (l0 + K <= L), converted later by
+// unpack_run: the loads can be issued well before the values are needed, e.g. ahead of
+// a barrier.  16-byte vectors, or one of 8 bytes where the run is no longer.
+template <typename T, int K>
+struct RawRun {
+    static constexpr bool kHalf = K * sizeof(T) == 8;
+    static constexpr int kVecs = kHalf ? 1 : K / Storage<T>::kPerVec;
+    static_assert(kHalf || K % Storage<T>::kPerVec == 0, "whole vectors");
+    std::conditional_t<kHalf, u32x2, u32x4> w[kVecs];
+};
+template <typename T, int K, bool NT = false>
+__device__ __forceinline__ RawRun<T, K> load_raw(const T* __restrict__ row, int64_t l0) {
+    using R = RawRun<T, K>;
+    R r;
+#pragma unroll
+    for (int i = 0; i < R::kVecs; ++i) {
+        using V = std::conditional_t<R::kHalf, typename Storage<T>::Half, typename Storage<T>::Vec>;
+        const V* p = reinterpret_cast<const V*>(row + l0 + i * Storage<T>::kPerVec);
+        if constexpr (NT) r.w[i] = __builtin_nontemporal_load(p);
+        else r.w[i] = *p;
+    }
+    return r;
+}
+// The same, non-temporal: for inputs read once, so that they do not take cache space
+// from inputs that are read again.
+template <typename T, int K>
+__device__ __forceinline__ RawRun<T, K> load_raw_nt(const T* __restrict__ row, int64_t l0) {
+    return load_raw<T, K, true>(row, l0);
+}
+template <typename T, int K>
+__device__ __forceinline__ void unpack_run(const RawRun<T, K>& r, float* v) {
+    if constexpr (RawRun<T, K>::kHalf) {
+        float t[Storage<T>::kPerVec];
+        Storage<T>::unpack(u32x4{r.w[0].x, r.w[0].y, 0u, 0u}, t);
+#pragma unroll
+        for (int i = 0; i < K; ++i) v[i] = t[i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < RawRun<T, K>::kVecs; ++i) Storage<T>::unpack(r.w[i], v + i * Storage<T>::kPerVec);
+    }
+}
+
 // Load K consecutive elements starting at row[l0] (K a multiple of the vector width),
 // converting to float; elements at or beyond L read as `fill`.  With FULL the caller
 // guarantees l0 + K <= L, so the loads are unconditional (no control flow: the compiler
@@ -84,50 +131,12 @@ template <> struct Storage<bf16_t> {
 template <typename T, int K, bool FULL = false>
 __device__ __forceinline__ void load_run(const T* __restrict__ row, int64_t l0, int64_t L, float* v,
                                          float fill = 0.0f) {
-    constexpr int PV = Storage<T>::kPerVec;
-    static_assert(K % PV == 0, "K must be a multiple of the vector width");
     if (FULL || l0 + K <= L) {
-#pragma unroll
-        for (int i = 0; i < K / PV; ++i) {
-            const u32x4 w = *reinterpret_cast<const typename Storage<T>::Vec*>(row + l0 + i * PV);
-            Storage<T>::unpack(w, v + i * PV);
-        }
+        unpack_run(load_raw<T, K>(row, l0), v);
     } else {
 #pragma unroll
         for (int i = 0; i < K; ++i) v[i] = (l0 + i < L) ? Storage<T>::load1(row + l0 + i) : fill;
     }
-}
-
-// K consecutive elements at row[l0] as raw 16-byte vectors (l0 + K <= L), converted later by unpack_run: the loads can be issued well before the
-// values are needed, e.g. ahead of a barrier.
-template <typename T, int K>
-struct RawRun {
-    u32x4 w[K / Storage<T>::kPerVec];
-};
-template <typename T, int K>
-__device__ __forceinline__ RawRun<T, K> load_raw(const T* __restrict__ row, int64_t l0) {
-    constexpr int PV = Storage<T>::kPerVec;
-    RawRun<T, K> r;
-#pragma unroll
-    for (int i = 0; i < K / PV; ++i) r.w[i] = *reinterpret_cast<const typename Storage<T>::Vec*>(row + l0 + i * PV);
-    return r;
-}
-// The same, non-temporal: for inputs read once, so that they do not take cache space
-// from inputs that are read again.
-template <typename T, int K>
-__device__ __forceinline__ RawRun<T, K> load_raw_nt(const T* __restrict__ row, int64_t l0) {
-    constexpr int PV = Storage<T>::kPerVec;
-    RawRun<T, K> r;
-#pragma unroll
-    for (int i = 0; i < K / PV; ++i)
-        r.w[i] = __builtin_nontemporal_load(reinterpret_cast<const typename Storage<T>::Vec*>(row + l0 + i * PV));
-    return r;
-}
-template <typename T, int K>
-__device__ __forceinline__ void unpack_run(const RawRun<T, K>& r, float* v) {
-    constexpr int PV = Storage<T>::kPerVec;
-#pragma unroll
-    for (int i = 0; i < K / PV; ++i) Storage<T>::unpack(r.w[i], v + i * PV);
 }
 
 // Store K consecutive elements (rounding to T) at row[l0]; elements beyond L are dropped.
@@ -141,7 +150,14 @@ __device__ __forceinline__ void unpack_run(const RawRun<T, K>& r, float* v) {
 template <typename T, int K, bool FULL = false, bool NT = (K == Storage<T>::kPerVec)>
 __device__ __forceinline__ void store_run(T* __restrict__ row, int64_t l0, int64_t L, const float* v) {
     constexpr int PV = Storage<T>::kPerVec;
-    if (FULL || l0 + K <= L) {
+    if (K < PV && (FULL || l0 + K <= L)) {                // one 8-byte vector
+        static_assert(K >= PV || K * sizeof(T) == 8, "whole vectors");
+        float t[PV] = {};
+#pragma unroll
+        for (int i = 0; i < K && i < PV; ++i) t[i] = v[i];
+        const u32x4 w = Storage<T>::pack(t);
+        __builtin_nontemporal_store(u32x2{w.x, w.y}, reinterpret_cast<typename Storage<T>::Half*>(row + l0));
+    } else if (FULL || l0 + K <= L) {
 #pragma unroll
         for (int i = 0; i < K / PV; ++i) {
             auto* dst = reinterpret_cast<typename Storage<T>::Vec*>(row + l0 + i * PV);
@@ -210,6 +226,17 @@ PM_DPP_OPS(shl1, "row_shl:1")
 PM_DPP_OPS(shl2, "row_shl:2")
 PM_DPP_OPS(shl4, "row_shl:4")
 PM_DPP_OPS(shl8, "row_shl:8")
+// across rows: lane 15 of rows 0 and 2 to the rows after them; lane 31 to rows 2 and 3
+#define PM_DPP_BCAST(NAME, CTRL, ROWS)                                                      \
+    __device__ __forceinline__ void mul_##NAME(float& x) {                                 \
+        asm("s_nop 1\n\tv_mul_f32_dpp %0, %0, %0 " CTRL " row_mask:" ROWS " bank_mask:0xf" : "+v"(x)); \
+    }                                                                                       \
+    __device__ __forceinline__ void fmac_##NAME(float& h, float p) {                        \
+        asm("s_nop 1\n\tv_fmac_f32_dpp %0, %0, %1 " CTRL " row_mask:" ROWS " bank_mask:0xf" : "+v"(h) : "v"(p)); \
+    }
+PM_DPP_BCAST(bcast15, "row_bcast:15", "0xa")
+PM_DPP_BCAST(bcast31, "row_bcast:31", "0xc")
+#undef PM_DPP_BCAST
 #undef PM_DPP_OPS
 
 // Inclusive scan, inside each 16-lane row, of the affine maps x -> P x + H.
@@ -218,11 +245,15 @@ PM_DPP_OPS(shl8, "row_shl:8")
 // lanes 15..j (lane j's map applied last).
 __device__ __forceinline__ void dpp_tail_nop(float& x) { asm("s_nop 1" : "+v"(x)); }
 
-__device__ __forceinline__ void row_scan_up(float& P, float& H) {
+// The same over groups of 16, 32 or 64 lanes (whole rows of a wave).
+template <int LANES>
+__device__ __forceinline__ void lane_scan_up(float& P, float& H) {
     fmac_shr1(H, P); mul_shr1(P);
     fmac_shr2(H, P); mul_shr2(P);
     fmac_shr4(H, P); mul_shr4(P);
     fmac_shr8(H, P); mul_shr8(P);
+    if constexpr (LANES > 16) { fmac_bcast15(H, P); mul_bcast15(P); }
+    if constexpr (LANES > 32) { fmac_bcast31(H, P); mul_bcast31(P); }
     dpp_tail_nop(P);
 }
 __device__ __forceinline__ void row_scan_down(float& P, float& H) {

@@ -162,6 +162,29 @@ inline SegPlan scan_segments(int64_t batch, int64_t dim, int64_t seqlen, int64_t
     return {(units + per - 1) / per, per * kSegUnit};
 }
 
+// The forward's split and its lanes per channel (scan forward kernel; 16 lanes: blocks of 16
+// channels, 32: of 8, 64: of 4).  Times in us, bf16, saving states:
+//  - from 448 blocks of 16 channels: 16 lanes, unsplit (512 blocks, 4 x 8192 x 2048: 396
+//    against 444 with 32 lanes; 640: 261 both);
+//  - from 256 blocks, rows of up to 4096 tokens (from 384 blocks any): 32 lanes, unsplit, no
+//    aggregate pass (4 x 2048 x 1536: 89 against 105; 4 x 1024 x 1024: 50 against 63 in four
+//    segments).  Longer rows in 256 blocks are split: 2 x 8192 x 2048 takes 190 (short
+//    sequences, which an aggregate pass skips quickly) to 268 (long ones) split and 246 unsplit;
+//  - below that, rows split; where even single-unit segments leave less than one round of
+//    768 blocks of 16, 32 lanes (1 x 1000 x 512: 32 against 37), and 64 below 192 (1 x 256 x
+//    64: 19 against 22; 1 x 700 x 128: 32 against 38).
+struct FwdPlan {
+    SegPlan seg;
+    int lanes;
+};
+inline FwdPlan scan_fwd_plan(int64_t batch, int64_t dim, int64_t seqlen) {
+    const int64_t blocks = batch * ((dim + 15) / 16);
+    const int64_t units = (seqlen + kSegUnit - 1) / kSegUnit;
+    if (blocks >= 448) return {{1, units * kSegUnit}, 16};
+    if (blocks >= 256 && (seqlen <= 4096 || blocks >= 384)) return {{1, units * kSegUnit}, 32};
+    return {scan_segments(batch, dim, seqlen, kSegTargetFwd), blocks * units < 192 ? 64 : blocks * units < 768 ? 32 : 16};
+}
+
 hipError_t launch_scan_fwd(const ScanArgs& a, hipStream_t s);
 hipError_t launch_scan_bwd(const ScanArgs& a, hipStream_t s);
 hipError_t launch_check_pos(const int32_t* pos, int64_t batch, int64_t seqlen, int32_t continued,

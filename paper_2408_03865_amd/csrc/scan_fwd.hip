@@ -1,19 +1,20 @@
 // scan_fwd.hip -- packed selective scan, forward (Eqs. 1a, 1b, 2a; Alg. 2; §3.4).
 //
 // Layout of the work (gfx950, wave64):
-//  - a block is 4 waves = 16 rows of 16 lanes; each 16-lane DPP row owns one
-//    channel d of one batch row b, so a block covers 16 channels of one b;
-//  - each lane owns K consecutive tokens, a row owns a chunk of 16*K tokens, and
-//    the block walks the sequence chunk by chunk, carrying the state h[n] of
-//    every channel from one chunk to the next in registers;
-//  - B and C of the chunk (shared by the 16 channels) and the reset mask derived
-//    from the position indices are staged once per chunk in LDS as fp32 with a
-//    padded layout (conflict-free 16-byte reads), read from HBM with coalesced
-//    vector loads (§3.5);
+//  - a block is 4 waves; a group of LANES lanes (16, 32 or 64: whole DPP rows) owns one
+//    channel d of one batch row b, so a block covers 256 / LANES channels of one b;
+//  - each lane owns K = 256 / LANES consecutive tokens, a group owns a chunk of 256
+//    tokens, and the block walks the sequence chunk by chunk, carrying the state h[n] of
+//    every channel from one chunk to the next in LDS.  16 lanes need the fewest
+//    instructions (fold and scans are shared by 16 tokens), 32 and 64 give two and four
+//    times the waves and shorter chains where 16 leave SIMDs idle (scan_fwd_plan);
+//  - B and C of the chunk (shared by the block's channels) and the reset mask derived
+//    from the position indices are staged once per chunk in LDS as fp32 (conflict-free
+//    16-byte reads), read from HBM with coalesced vector loads (§3.5);
 //  - per state n the pair (Abar, Bbar x) = (exp(dt*A), dt*B*u) is folded over the
-//    lane's K tokens, the 16 lane aggregates are combined by an inclusive DPP
-//    scan inside the row, the chunk carry is applied, and the lane replays its K
-//    tokens from its start state to form h and y += C h.
+//    lane's K tokens, the lane aggregates are combined by an inclusive DPP scan over the
+//    group, the chunk carry is applied, and the lane replays its K tokens from its start
+//    state to form h and y += C h.
 //  - Reset (Alg. 2): Abar = exp2(dt * A*log2e + M) with M = -inf on a token whose
 //    position index is 0, so the multiplier is exactly 0 there at no extra cost;
 //    a product range that contains a start is therefore 0 inside the fold and the
@@ -33,18 +34,19 @@ namespace pm {
 namespace {
 
 constexpr int kN = 16;              // d_state
-constexpr int kRows = 16;           // channels per block
 constexpr int kThreads = 256;
 constexpr int kStride = 128;        // saved-state token stride (PACKMAMBA_STATE_STRIDE)
 
-template <int K>
+constexpr int kCH = 256;                // tokens per chunk
+
+template <int LANES>
 struct __attribute__((aligned(16))) FwdSmem {
-    // [state][lane][token], each lane's segment padded by 4 floats so that the
-    // 16-byte reads of 8 consecutive lanes fall in distinct banks
-    static constexpr int kSeg = K + 4;
-    float B[kN][16][kSeg];
-    float C[kN][16][kSeg];
-    float M[16][kSeg];          // 0, or -inf on a sequence start
+    // [state][four of the lane's tokens][lane][token]: consecutive lanes read consecutive
+    // 16-byte words
+    static constexpr int K = kCH / LANES, kRows = kThreads / LANES;
+    float B[kN][K / 4][LANES][4];
+    float C[kN][K / 4][LANES][4];
+    float M[K / 4][LANES][4];   // 0, or -inf on a sequence start
     float A2[kRows][kN];        // A * log2(e)
     float carry[kRows][kN];     // state after the previous chunk
     float pseg[kRows][kN];      // aggregate pass: product of the multipliers so far
@@ -94,16 +96,17 @@ __device__ __forceinline__ float chain_maps(const float2* __restrict__ maps, int
 }
 
 // AGG: aggregate pass over one segment (no C, no outputs), writes its map (P, H).
-template <typename T, typename TO, int K, bool AGG>
+template <typename T, typename TO, int LANES, bool AGG>
 __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
-    constexpr int CH = 16 * K;
     constexpr int PV = Storage<T>::kPerVec;
-    using Smem = FwdSmem<K>;
+    using Smem = FwdSmem<LANES>;
+    constexpr int K = Smem::K, kRows = Smem::kRows, CH = kCH;
+    constexpr bool AHEAD = LANES > 16;            // registers to spare: load a chunk ahead
     __shared__ Smem sm;
 
     const int tid = threadIdx.x;
-    const int j = tid & 15;                       // lane position inside the row
-    const int r = tid >> 4;                       // row (channel) inside the block
+    const int j = tid & (LANES - 1);              // lane position inside the channel's group
+    const int r = tid / LANES;                    // channel inside the block
     const int64_t b = blockIdx.y;
     const int seg = blockIdx.z;
     const int64_t d_raw = (int64_t)blockIdx.x * kRows + r;
@@ -120,7 +123,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
     const T* Cb = static_cast<const T*>(p.C) + b * kN * L;
     const int32_t* pr = p.pos + b * L;
 
-    {
+    if (tid < kRows * kN) {
         const int rr = tid >> 4, n = tid & 15;
         const int64_t dd = min((int64_t)blockIdx.x * kRows + rr, p.dim - 1);
         sm.A2[rr][n] = p.A[dd * kN + n] * kLog2e;
@@ -136,36 +139,61 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
     const float dbias = p.delta_bias ? p.delta_bias[d] : 0.0f;
 
     const int64_t nchunk = (L + CH - 1) / CH;
+    // The inputs of one full chunk that this thread loads, as stored: its own tokens of u,
+    // delta and z, its part of the block's B and C, and a position index.
+    constexpr int NB = kN * CH / (kThreads * PV);
+    constexpr bool EARLY = AHEAD || NB == 2;      // B and C too before anything is staged
+    struct Inputs {
+        RawRun<T, K> u, d, z;
+        RawRun<T, PV> b[NB], c[NB];
+        int pos;
+    } in;
+    const auto load_inputs = [&](int64_t c) {
+        const int64_t lb = c * CH, l0 = lb + (int64_t)j * K;
+        in.u = load_raw<T, K>(ur, l0);
+        in.d = load_raw<T, K>(dr, l0);
+        if (AHEAD && !AGG && zr) in.z = load_raw<T, K>(zr, l0);
+#pragma unroll
+        for (int i = 0; i < (EARLY ? NB : 0); ++i) {
+            const int idx = (i * kThreads + tid) * PV, n = idx / CH, t = idx - n * CH;
+            in.b[i] = load_raw<T, PV>(Bb + (int64_t)n * L, lb + t);
+            if (!AGG) in.c[i] = load_raw<T, PV>(Cb + (int64_t)n * L, lb + t);
+        }
+        in.pos = pr[lb + tid];
+    };
     // One chunk; FULL (block-uniform) means the chunk lies inside the row, so every load
-    // and store is unconditional.
-    auto chunk = [&](auto full_tag, const int64_t c) {
+    // and store is unconditional.  `next`: the chunk to load ahead of the state loop, or -1.
+    auto chunk = [&](auto full_tag, const int64_t c, const int64_t next) {
         constexpr bool FULL = decltype(full_tag)::value;
         const int64_t lb = c * CH;
         const int64_t l0 = lb + (int64_t)j * K;
         // this lane's inputs, loaded first in a full chunk so that their latency
         // overlaps the staging below
-        RawRun<T, K> wu, wd;
-        if constexpr (FULL) {
-            wu = load_raw<T, K>(ur, l0);
-            wd = load_raw<T, K>(dr, l0);
-        }
+        if constexpr (FULL && !AHEAD) load_inputs(c);
         // ---- stage B, C and the reset mask of this chunk in LDS ----
-        for (int idx = tid * PV; idx < kN * CH; idx += kThreads * PV) {
-            const int n = idx / CH, t = idx - n * CH;
+        static_assert(kThreads == CH, "a thread stages one position index");
+#pragma unroll(EARLY ? NB : 1)
+        for (int i = 0; i < NB; ++i) {
+            const int idx = (i * kThreads + tid) * PV, n = idx / CH, t = idx - n * CH;
             float vb[PV], vc[PV];
-            load_run<T, PV, FULL>(Bb + (int64_t)n * L, lb + t, L, vb);
-            if (!AGG) load_run<T, PV, FULL>(Cb + (int64_t)n * L, lb + t, L, vc);
-            float* db = &sm.B[n][t / K][t % K];
-            float* dc = &sm.C[n][t / K][t % K];
+            if constexpr (FULL && EARLY) {
+                unpack_run(in.b[i], vb);
+                if (!AGG) unpack_run(in.c[i], vc);
+            } else {
+                load_run<T, PV, FULL>(Bb + (int64_t)n * L, lb + t, L, vb);
+                if (!AGG) load_run<T, PV, FULL>(Cb + (int64_t)n * L, lb + t, L, vc);
+            }
 #pragma unroll
-            for (int q = 0; q < PV; ++q) {
-                db[q] = vb[q];
-                if (!AGG) dc[q] = vc[q];
+            for (int q = 0; q < PV; q += 4) {
+                const int h = (t + q) % K / 4, l = (t + q) / K;
+                *reinterpret_cast<f32x4*>(sm.B[n][h][l]) = f32x4{vb[q], vb[q + 1], vb[q + 2], vb[q + 3]};
+                if (!AGG) *reinterpret_cast<f32x4*>(sm.C[n][h][l]) = f32x4{vc[q], vc[q + 1], vc[q + 2], vc[q + 3]};
             }
         }
-        for (int t = tid; t < CH; t += kThreads) {
-            const int64_t l = lb + t;
-            sm.M[t / K][t % K] = ((FULL || l < L) && pr[l] == 0) ? -INFINITY : 0.0f;
+        {
+            const int64_t l = lb + tid;
+            const int ps = FULL ? in.pos : l < L ? pr[l] : 1;
+            sm.M[tid % K / 4][tid / K][tid % 4] = ps == 0 ? -INFINITY : 0.0f;
         }
         __syncthreads();
 
@@ -174,8 +202,8 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
         {
             float uv[K];
             if constexpr (FULL) {
-                unpack_run(wu, uv);
-                unpack_run(wd, dt);
+                unpack_run(in.u, uv);
+                unpack_run(in.d, dt);
             } else {
                 load_run<T, K, FULL>(ur, l0, L, uv);
                 load_run<T, K, FULL>(dr, l0, L, dt);
@@ -191,10 +219,13 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
             }
 #pragma unroll
             for (int k = 0; k < K; k += 4) {
-                const f32x4 m = *reinterpret_cast<const f32x4*>(&sm.M[j][k]);
+                const f32x4 m = *reinterpret_cast<const f32x4*>(sm.M[k / 4][j]);
                 M[k] = m.x; M[k + 1] = m.y; M[k + 2] = m.z; M[k + 3] = m.w;
             }
         }
+        // the next chunk's inputs, on their way while this one's states are worked through
+        const RawRun<T, K> wz = in.z;
+        if (AHEAD && next >= 0) load_inputs(next);
         // product of the lane's multipliers as one exp2 (0 if the lane holds a start)
         float S = 0.0f, Mf = 0.0f;
 #pragma unroll
@@ -204,14 +235,14 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
 #pragma unroll 1
         for (int n = 0; n < kN; ++n) {
             // aggregate: a (channel, state) whose multiplier product is already exactly 0
-            // is final; the wave skips the state when that holds for its 4 channels
+            // is final; the wave skips the state when that holds for all its channels
             if (AGG && __all(sm.pseg[r][n] == 0.0f)) continue;
             const float A2n = sm.A2[r][n];
             const float cin = sm.carry[r][n];
             float a[K], bx[K];
 #pragma unroll
             for (int k = 0; k < K; k += 4) {
-                const f32x4 bv = *reinterpret_cast<const f32x4*>(&sm.B[n][j][k]);
+                const f32x4 bv = *reinterpret_cast<const f32x4*>(sm.B[n][k / 4][j]);
                 const float bb[4] = {bv.x, bv.y, bv.z, bv.w};
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -224,11 +255,11 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
 #pragma unroll
             for (int k = 1; k < K; ++k) H = fmaf(a[k], H, bx[k]);
             float P = fast_exp2(fmaf(S, A2n, Mf));
-            row_scan_up(P, H);
+            lane_scan_up<LANES>(P, H);
             if (AGG) {
-                // lane 15's (P, H) is the chunk's map; the chunks after it are already
+                // the last lane's (P, H) is the chunk's map; the chunks after it are already
                 // composed in (pseg, carry), which becomes (pseg P, pseg H + carry)
-                if (j == 15) {
+                if (j == LANES - 1) {
                     const float pa = sm.pseg[r][n];
                     sm.carry[r][n] = fmaf(pa, H, sm.carry[r][n]);
                     sm.pseg[r][n] = pa * P;
@@ -236,11 +267,12 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
                 continue;
             }
             const float hend = fmaf(P, cin, H);               // state after this lane's last token
-            float h = dpp<kRowShr1>(cin, hend);               // state before this lane's first token
-            if (j == 15) sm.carry[r][n] = hend;               // state after the chunk
+            float h = dpp<LANES == 16 ? kRowShr1 : kWaveShr1>(cin, hend);   // state before this lane's first token
+            if (LANES == 32) h = j == 0 ? cin : h;            // lane 32's came from the other channel
+            if (j == LANES - 1) sm.carry[r][n] = hend;               // state after the chunk
 #pragma unroll
             for (int k = 0; k < K; k += 4) {
-                const f32x4 cv = *reinterpret_cast<const f32x4*>(&sm.C[n][j][k]);
+                const f32x4 cv = *reinterpret_cast<const f32x4*>(sm.C[n][k / 4][j]);
                 const float cc[4] = {cv.x, cv.y, cv.z, cv.w};
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -260,7 +292,8 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
         if (!AGG && active && (orow || p.dzf)) {
             if (zr) {
                 float zv[K], g[K];
-                load_run<T, K, FULL>(zr, l0, L, zv);
+                if constexpr (FULL && AHEAD) unpack_run(wz, zv);
+                else load_run<T, K, FULL>(zr, l0, L, zv);
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     const float sz = sigmoid_f(zv[k]);
@@ -273,7 +306,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
 #pragma unroll
                     for (int i = 0; i < K / 4; ++i)
                         __builtin_nontemporal_store(f32x4{g[4 * i], g[4 * i + 1], g[4 * i + 2], g[4 * i + 3]},
-                                                    reinterpret_cast<f32x4*>(fr + dzf_vec(c, i, j)));
+                                                    reinterpret_cast<f32x4*>(fr + dzf_vec(c, (j * K + 4 * i) % 16 / 4, (j * K + 4 * i) / 16)));
                 }
             }
             if (orow) store_run<TO, K, FULL>(orow, l0, L, y);
@@ -287,22 +320,24 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
         // the product of the multipliers is exactly 0 for every channel and state of the
         // block (a sequence start, or underflow of a long decay), the earlier chunks
         // contribute exactly nothing, and the walk stops.
+        if (AHEAD) load_inputs(c1 - 1);            // (a segment that is aggregated lies inside the row)
         for (int64_t c = c1 - 1; c >= c0; --c) {
-            if ((c + 1) * CH <= L) chunk(std::true_type{}, c);
-            else chunk(std::false_type{}, c);
-            if (!__syncthreads_or(sm.pseg[tid >> 4][tid & 15] != 0.0f)) break;
+            chunk(std::true_type{}, c, c > c0 ? c - 1 : -1);
+            if (!__syncthreads_or(tid < kRows * kN && sm.pseg[0][tid] != 0.0f)) break;
         }
     } else {
+        const int64_t full = L / CH;              // chunks that lie inside the row
+        if (AHEAD && c0 < full) load_inputs(c0);
         for (int64_t c = c0; c < c1; ++c) {
-            if ((c + 1) * CH <= L) chunk(std::true_type{}, c);
-            else chunk(std::false_type{}, c);
+            if (c < full) chunk(std::true_type{}, c, c + 1 < min(c1, full) ? c + 1 : -1);
+            else chunk(std::false_type{}, c, -1);
         }
     }
     if (AGG) {
         __syncthreads();
         const int rr = tid >> 4, n = tid & 15;
         const int64_t dd = (int64_t)blockIdx.x * kRows + rr;
-        if (dd < p.dim) {
+        if (rr < kRows && dd < p.dim) {
             p.agg[((b * p.dim + dd) * p.nseg + seg) * kN + n] = float2{sm.pseg[rr][n], sm.carry[rr][n]};
         }
     } else if (p.hfinal && c1 == nchunk) {
@@ -310,7 +345,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
         // the row end are identities)
         const int rr = tid >> 4, n = tid & 15;
         const int64_t dd = (int64_t)blockIdx.x * kRows + rr;
-        if (dd < p.dim) p.hfinal[(b * p.dim + dd) * kN + n] = sm.carry[rr][n];
+        if (rr < kRows && dd < p.dim) p.hfinal[(b * p.dim + dd) * kN + n] = sm.carry[rr][n];
     }
 }
 
@@ -386,9 +421,30 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_short_kernel(FwdParams p) {
     if (p.hfinal && active) *reinterpret_cast<f32x4*>(p.hfinal + row * kN + 4 * q) = h;
 }
 
-template <typename T, typename TO, int K>
+// Lanes per channel of the aggregate pass, whatever the main pass has: a wave of two
+// channels skips a state as soon as both are done, and its chains are half as long as with
+// four (1 x 65536 x 2048 with three long sequences: the whole call 1171 -> 1037 us; 64
+// lanes 1121, pieces of a quarter segment 1041).
+constexpr int kAggLanes = 32;
+
+template <typename T, typename TO, int LANES>
+hipError_t launch_lanes(const ScanArgs& a, const FwdParams& p, hipStream_t s) {
+    constexpr int kRows = FwdSmem<LANES>::kRows;
+    const dim3 grid((unsigned)((a.dim + kRows - 1) / kRows), (unsigned)a.batch, (unsigned)p.nseg);
+    if (p.nseg > 1) {
+        // aggregate every segment but the last
+        constexpr int kAggRows = FwdSmem<kAggLanes>::kRows;
+        hipLaunchKernelGGL((scan_fwd_kernel<T, TO, kAggLanes, true>),
+                           dim3((unsigned)((a.dim + kAggRows - 1) / kAggRows), grid.y, grid.z - 1), dim3(kThreads), 0, s, p);
+        if (hipError_t e = hipGetLastError()) return e;
+    }
+    hipLaunchKernelGGL((scan_fwd_kernel<T, TO, LANES, false>), grid, dim3(kThreads), 0, s, p);
+    return hipGetLastError();
+}
+
+template <typename T, typename TO>
 hipError_t launch_t(const ScanArgs& a, hipStream_t s) {
-    static_assert(16 * K == kDzfChunk && K == 16, "the dz factor layout follows the forward's chunk");
+    static_assert(kCH == kDzfChunk, "the dz factor layout follows the forward's chunk");
     FwdParams p;
     p.u = a.u; p.delta = a.delta; p.A = a.A; p.B = a.B; p.C = a.C; p.D = a.D; p.z = a.z;
     p.delta_bias = a.delta_bias; p.pos = a.pos; p.out = a.out; p.states = a.states;
@@ -402,30 +458,26 @@ hipError_t launch_t(const ScanArgs& a, hipStream_t s) {
                            dim3((unsigned)((a.dim + kShortCh - 1) / kShortCh), (unsigned)a.batch), dim3(kThreads), 0, s, p);
         return hipGetLastError();
     }
-    const SegPlan sp = scan_segments(a.batch, a.dim, a.seqlen, kSegTargetFwd);
-    static_assert(kSegUnit % (16 * K) == 0, "segments hold whole chunks");
-    p.seg_chunks = sp.seg_len / (16 * K);
+    const FwdPlan plan = scan_fwd_plan(a.batch, a.dim, a.seqlen);
+    const SegPlan sp = plan.seg;
+    static_assert(kSegUnit % kCH == 0, "segments hold whole chunks");
+    p.seg_chunks = sp.seg_len / kCH;
     p.nseg = (int)sp.nseg;
     p.agg = reinterpret_cast<float2*>(a.ws_agg);
-    const unsigned groups = (unsigned)((a.dim + kRows - 1) / kRows);
-    if (sp.nseg > 1) {
-        // aggregate every segment but the last
-        hipLaunchKernelGGL((scan_fwd_kernel<T, TO, K, true>), dim3(groups, (unsigned)a.batch, (unsigned)(sp.nseg - 1)),
-                           dim3(kThreads), 0, s, p);
-        if (hipError_t e = hipGetLastError()) return e;
+    switch (plan.lanes) {
+        case 64: return launch_lanes<T, TO, 64>(a, p, s);
+        case 32: return launch_lanes<T, TO, 32>(a, p, s);
+        default: return launch_lanes<T, TO, 16>(a, p, s);
     }
-    hipLaunchKernelGGL((scan_fwd_kernel<T, TO, K, false>), dim3(groups, (unsigned)a.batch, (unsigned)sp.nseg),
-                       dim3(kThreads), 0, s, p);
-    return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_scan_fwd(const ScanArgs& a, hipStream_t s) {
     switch (a.dtype) {
-        case 1: return launch_t<bf16_t, bf16_t, 16>(a, s);
-        case 2: return launch_t<bf16_t, float, 16>(a, s);
-        default: return launch_t<float, float, 16>(a, s);
+        case 1: return launch_t<bf16_t, bf16_t>(a, s);
+        case 2: return launch_t<bf16_t, float>(a, s);
+        default: return launch_t<float, float>(a, s);
     }
 }
 
