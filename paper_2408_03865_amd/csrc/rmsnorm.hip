@@ -3,194 +3,321 @@
 // packing leaves it unchanged (§3.2); it is here so that every step of the block
 // runs in this library's kernels or in plain GEMMs.
 //
-// A block of 1024 threads owns a tile of 64 consecutive tokens of one batch row.
-// Thread (slice s, group g) holds tokens 8g .. 8g+7 of the tile (one 16-byte bf16
-// vector, two fp32 ones) of the features s, s+128, s+256, ...; the 8 groups of a
-// slice are consecutive lanes, so each load of a wave reads 8 feature rows of 128
-// contiguous bytes.  Many slices keep the loop over the features short, which
-// matters for short rows (few tiles).  Per-token sums over the features go through LDS in a fixed
-// order.  The second sweep over the tile re-reads its inputs; a tile is
-// 64 x dim elements, which the caches hold between the sweeps.
+// A block owns a tile of consecutive tokens of one batch row: GROUPS lanes side by side,
+// each with one 16-byte vector of tokens, so that every feature row gives GROUPS x 16
+// contiguous bytes, and THREADS / GROUPS slices of the features.  A thread keeps the
+// vectors of its first kKept features in registers from the sum over the features to the
+// second sweep; features beyond those are read again.
+// Bound by HBM where there are tiles enough for the GPU.  Us, forward and backward, against
+// 1024 threads that keep nothing and 8 tokens per lane in both types:
+//   8 x 4096 x 2048 bf16 (67 M elements)  60, 154   before 71, 173
+//   8 x 4096 x 2048 fp32                 108, 295   before 178, 356
+//   2 x 3001 x 2560 bf16                  55,  89   before 143, 284
+// 64-byte rows of a tile (4 groups) make up for few tiles, but cost the large shapes their
+// HBM pages (backward 240 us at the first of these), so they are used below 512 tiles.
 #include "common.hpp"
 #include "launch.hpp"
 
 namespace pm {
 namespace {
 
-constexpr int kThreads = 1024;
-constexpr int kGroups = 8;                   // token groups per tile
-constexpr int kTok = 8;                      // tokens per group
-constexpr int kTile = kGroups * kTok;        // tokens per tile
-constexpr int kSlices = kThreads / kGroups;  // feature slices
-static_assert(kTile == kRmsTile, "tile size shared with the workspace sizing");
+// Features a thread keeps in registers (64 VGPRs of x and dh in the backward; with 16 the
+// forward spilled at 1024 threads: 172 us against 62 at 8 x 4096 x 2048).
+constexpr int kKept = 8;
 
+// (batch row) x (tiles per row) + tile of this block.  Blocks go to the 8 XCDs in turn; with
+// 64-byte rows of a tile, the two tiles that share 128-byte lines go to the same one
+// (2 x 3001 x 2560 bf16: backward 89 us against 102).
+template <int GROUPS>
+__device__ __forceinline__ int64_t tile_id() {
+    const int64_t id = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    const int64_t g = id / 16 * 16, r = id - g;
+    if (GROUPS >= 8 || g + 16 > (int64_t)gridDim.x * gridDim.y) return id;
+    return g + (r % 8) * 2 + r / 8;
+}
+
+template <int GROUPS, int THREADS, int TOK>
 struct __attribute__((aligned(16))) RmsSmem {
+    static constexpr int kSlices = THREADS / GROUPS, kTile = GROUPS * TOK;
+    static constexpr int kParts = THREADS / kTile;       // first-level sums of each token
     float red[kSlices][kTile];   // per-slice values of each token
+    float part[kParts][kTile];
     float tot[kTile];            // their sums
 };
 
-// Sum over the slices of each token's per-slice value, in slice order; every
-// thread gets its 8 tokens' totals.
-__device__ __forceinline__ void slice_sum(float (&v)[kTok], RmsSmem& sm, int sl, int grp) {
-    *reinterpret_cast<f32x4*>(&sm.red[sl][grp * kTok]) = f32x4{v[0], v[1], v[2], v[3]};
-    *reinterpret_cast<f32x4*>(&sm.red[sl][grp * kTok + 4]) = f32x4{v[4], v[5], v[6], v[7]};
+// Sum over the slices of each token's per-slice value, in a fixed order; every thread gets
+// its own tokens' totals.
+template <int GROUPS, int THREADS, int TOK>
+__device__ __forceinline__ void slice_sum(float (&v)[TOK], RmsSmem<GROUPS, THREADS, TOK>& sm, int sl, int grp) {
+    using S = RmsSmem<GROUPS, THREADS, TOK>;
+#pragma unroll
+    for (int k = 0; k < TOK; k += 4)
+        *reinterpret_cast<f32x4*>(&sm.red[sl][grp * TOK + k]) = f32x4{v[k], v[k + 1], v[k + 2], v[k + 3]};
     __syncthreads();
-    if (threadIdx.x < kTile) {
-        float a = 0.0f;
-        for (int q = 0; q < kSlices; ++q) a += sm.red[q][threadIdx.x];
-        sm.tot[threadIdx.x] = a;
+    constexpr int kPer = S::kSlices / S::kParts;
+    const int tok = threadIdx.x % S::kTile, q = threadIdx.x / S::kTile;
+    float a = sm.red[q * kPer][tok];
+#pragma unroll
+    for (int i = 1; i < kPer; ++i) a += sm.red[q * kPer + i][tok];
+    sm.part[q][tok] = a;
+    __syncthreads();
+    if (threadIdx.x < S::kTile) {
+        a = sm.part[0][tok];
+#pragma unroll
+        for (int i = 1; i < S::kParts; ++i) a += sm.part[i][tok];
+        sm.tot[tok] = a;
     }
     __syncthreads();
-    const f32x4 a = *reinterpret_cast<const f32x4*>(&sm.tot[grp * kTok]);
-    const f32x4 c = *reinterpret_cast<const f32x4*>(&sm.tot[grp * kTok + 4]);
-    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-    v[4] = c.x; v[5] = c.y; v[6] = c.z; v[7] = c.w;
+#pragma unroll
+    for (int k = 0; k < TOK; k += 4) {
+        const f32x4 t = *reinterpret_cast<const f32x4*>(&sm.tot[grp * TOK + k]);
+        v[k] = t.x; v[k + 1] = t.y; v[k + 2] = t.z; v[k + 3] = t.w;
+    }
 }
 
-template <typename T, typename TO>
-__global__ __launch_bounds__(kThreads) void rmsnorm_fwd_kernel(const T* __restrict__ x,
-                                                               const float* __restrict__ w, float eps,
-                                                               TO* __restrict__ out, float* __restrict__ rstd,
-                                                               int64_t dim, int64_t L) {
-    __shared__ RmsSmem sm;
-    const int tid = threadIdx.x, grp = tid & (kGroups - 1), sl = tid / kGroups;
-    const int64_t b = blockIdx.y;
-    const int64_t l0 = (int64_t)blockIdx.x * kTile + grp * kTok;
+template <typename T, typename TO, int GROUPS, int THREADS>
+__global__ __launch_bounds__(THREADS) void rmsnorm_fwd_kernel(const T* __restrict__ x, const float* __restrict__ w,
+                                                              float eps, TO* __restrict__ out,
+                                                              float* __restrict__ rstd, int64_t dim, int64_t L) {
+    constexpr int TOK = Storage<T>::kPerVec;
+    using Smem = RmsSmem<GROUPS, THREADS, TOK>;
+    constexpr int SL = Smem::kSlices;
+    __shared__ Smem sm;
+    const int grp = threadIdx.x % GROUPS, sl = threadIdx.x / GROUPS;
+    const int64_t id = tile_id<GROUPS>();
+    const int64_t b = id / gridDim.x;
+    const int64_t l0 = (id - b * gridDim.x) * Smem::kTile + grp * TOK;
     const T* xb = x + b * dim * L;
     TO* ob = out + b * dim * L;
-    float s[kTok] = {};
-    for (int64_t f = sl; f < dim; f += kSlices) {
-        float v[kTok];
-        load_run<T, kTok>(xb + f * L, l0, L, v);
+    // FULL (block-uniform): the tile lies inside the row
+    const auto body = [&](auto full_tag) {
+        constexpr bool FULL = decltype(full_tag)::value;
+        constexpr int C = FULL ? kKept : 0;                     // features kept in registers
+        const int64_t lane = sl * L + l0;                    // this lane's vector of feature sl
+        RawRun<T, TOK> xr[kKept];
 #pragma unroll
-        for (int k = 0; k < kTok; ++k) s[k] = fmaf(v[k], v[k], s[k]);
-    }
-    slice_sum(s, sm, sl, grp);
-    float r[kTok];
+        for (int i = 0; i < C; ++i) {
+            xr[i] = RawRun<T, TOK>{};
+            if (sl + i * SL < dim) xr[i] = load_raw<T, TOK>(xb + i * SL * L + lane, 0);
+        }
+        float s[TOK] = {};
+        const auto square = [&](const float (&v)[TOK]) {
 #pragma unroll
-    for (int k = 0; k < kTok; ++k) r[k] = 1.0f / sqrtf(s[k] / (float)dim + eps);
-    if (sl == 0) {
+            for (int k = 0; k < TOK; ++k) s[k] = fmaf(v[k], v[k], s[k]);
+        };
 #pragma unroll
-        for (int k = 0; k < kTok; ++k)
-            if (l0 + k < L) rstd[b * L + l0 + k] = r[k];
-    }
-    for (int64_t f = sl; f < dim; f += kSlices) {
-        float v[kTok];
-        load_run<T, kTok>(xb + f * L, l0, L, v);
-        const float wf = w[f];
+        for (int i = 0; i < C; ++i) {
+            float v[TOK];
+            unpack_run(xr[i], v);
+            square(v);
+        }
+        for (int64_t f = sl + C * SL; f < dim; f += SL) {
+            float v[TOK];
+            load_run<T, TOK, FULL>(xb + f * L, l0, L, v);
+            square(v);
+        }
+        slice_sum(s, sm, sl, grp);
+        float r[TOK];
 #pragma unroll
-        for (int k = 0; k < kTok; ++k) v[k] = v[k] * r[k] * wf;
-        store_run<TO, kTok>(ob + f * L, l0, L, v);
-    }
+        for (int k = 0; k < TOK; ++k) r[k] = 1.0f / sqrtf(s[k] / (float)dim + eps);
+        if (sl == 0) {
+#pragma unroll
+            for (int k = 0; k < TOK; ++k)
+                if (FULL || l0 + k < L) rstd[b * L + l0 + k] = r[k];
+        }
+        const auto scale = [&](float (&v)[TOK], int64_t fb) {      // feature fb + sl
+            const int64_t f = fb + sl;
+            const float wv = w[f];
+#pragma unroll
+            for (int k = 0; k < TOK; ++k) v[k] = v[k] * r[k] * wv;
+            if constexpr (FULL) store_run<TO, TOK, true>(ob + fb * L + lane, 0, L, v);
+            else store_run<TO, TOK>(ob + f * L, l0, L, v);
+        };
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            float v[TOK];
+            unpack_run(xr[i], v);
+            if (sl + i * SL < dim) scale(v, i * SL);
+        }
+        for (int64_t f = sl + C * SL; f < dim; f += SL) {
+            float v[TOK];
+            load_run<T, TOK, FULL>(xb + f * L, l0, L, v);
+            scale(v, f - sl);
+        }
+    };
+    if (l0 - grp * TOK + Smem::kTile <= L) body(std::true_type{});
+    else body(std::false_type{});
 }
 
 // dx = r (dh w - x r^2 s / dim) (+ dres), s = sum_f dh w x at each token;
 // partial[b, tile, f] = sum over the tile's tokens of dh x r.
-template <typename T, typename TO>
-__global__ __launch_bounds__(kThreads) void rmsnorm_bwd_kernel(
+template <typename T, typename TO, int GROUPS, int THREADS>
+__global__ __launch_bounds__(THREADS) void rmsnorm_bwd_kernel(
     const T* __restrict__ x, const float* __restrict__ w, const float* __restrict__ rstd,
     const T* __restrict__ dh, const T* __restrict__ dres, TO* __restrict__ dx,
     float* __restrict__ partial, int64_t dim, int64_t L) {
-    __shared__ RmsSmem sm;
-    const int tid = threadIdx.x, grp = tid & (kGroups - 1), sl = tid / kGroups;
-    const int64_t b = blockIdx.y;
-    const int64_t tile = blockIdx.x;
-    const int64_t l0 = tile * kTile + grp * kTok;
+    constexpr int TOK = Storage<T>::kPerVec;
+    using Smem = RmsSmem<GROUPS, THREADS, TOK>;
+    constexpr int SL = Smem::kSlices;
+    __shared__ Smem sm;
+    const int grp = threadIdx.x % GROUPS, sl = threadIdx.x / GROUPS;
+    const int64_t id = tile_id<GROUPS>();
+    const int64_t b = id / gridDim.x;
+    const int64_t l0 = (id - b * gridDim.x) * Smem::kTile + grp * TOK;
     const int64_t off = b * dim * L;
-    float s[kTok] = {};
-    for (int64_t f = sl; f < dim; f += kSlices) {
-        float xv[kTok], gv[kTok];
-        load_run<T, kTok>(x + off + f * L, l0, L, xv);
-        load_run<T, kTok>(dh + off + f * L, l0, L, gv);
-        const float wf = w[f];
+    const T* xb = x + off;
+    const T* gb = dh + off;
+    float* pb = partial + id * dim;
+    // FULL (block-uniform): the tile lies inside the row
+    const auto body = [&](auto full_tag) {
+        constexpr bool FULL = decltype(full_tag)::value;
+        constexpr int C = FULL ? kKept : 0;                     // features kept in registers
+        const int64_t lane = sl * L + l0;                    // this lane's vector of feature sl
+        RawRun<T, TOK> xr[kKept], gr[kKept];
 #pragma unroll
-        for (int k = 0; k < kTok; ++k) s[k] = fmaf(gv[k] * wf, xv[k], s[k]);
-    }
-    slice_sum(s, sm, sl, grp);
-    float r[kTok], c[kTok];
-#pragma unroll
-    for (int k = 0; k < kTok; ++k) {
-        r[k] = (l0 + k < L) ? rstd[b * L + l0 + k] : 0.0f;
-        c[k] = r[k] * r[k] * s[k] / (float)dim;
-    }
-    float* pb = partial + (b * gridDim.x + tile) * dim;
-    for (int64_t f = sl; f < dim; f += kSlices) {
-        float xv[kTok], gv[kTok], o[kTok];
-        load_run<T, kTok>(x + off + f * L, l0, L, xv);
-        load_run<T, kTok>(dh + off + f * L, l0, L, gv);
-        if (dres) load_run<T, kTok>(dres + off + f * L, l0, L, o);
-        const float wf = w[f];
-        float pw = 0.0f;
-#pragma unroll
-        for (int k = 0; k < kTok; ++k) {
-            const float v = r[k] * (gv[k] * wf - xv[k] * c[k]);
-            o[k] = dres ? o[k] + v : v;
-            pw = fmaf(gv[k] * xv[k], r[k], pw);      // 0 past the row end: loads read 0
+        for (int i = 0; i < C; ++i) {
+            xr[i] = gr[i] = RawRun<T, TOK>{};
+            if (sl + i * SL < dim) {
+                xr[i] = load_raw<T, TOK>(xb + i * SL * L + lane, 0);
+                gr[i] = load_raw<T, TOK>(gb + i * SL * L + lane, 0);
+            }
         }
-        store_run<TO, kTok>(dx + off + f * L, l0, L, o);
-        // over the 8 groups of the slice (consecutive lanes), in a fixed order
-        pw += __shfl_xor(pw, 1, kGroups);
-        pw += __shfl_xor(pw, 2, kGroups);
-        pw += __shfl_xor(pw, 4, kGroups);
-        if (grp == 0) pb[f] = pw;
-    }
+        float s[TOK] = {};
+        const auto dot = [&](const float (&xv)[TOK], const float (&gv)[TOK], float wv) {
+#pragma unroll
+            for (int k = 0; k < TOK; ++k) s[k] = fmaf(gv[k] * wv, xv[k], s[k]);
+        };
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            float xv[TOK], gv[TOK];
+            unpack_run(xr[i], xv);
+            unpack_run(gr[i], gv);
+            if (sl + i * SL < dim) dot(xv, gv, w[sl + i * SL]);
+        }
+        for (int64_t f = sl + C * SL; f < dim; f += SL) {
+            float xv[TOK], gv[TOK];
+            load_run<T, TOK, FULL>(xb + f * L, l0, L, xv);
+            load_run<T, TOK, FULL>(gb + f * L, l0, L, gv);
+            dot(xv, gv, w[f]);
+        }
+        float r[TOK], c[TOK];
+#pragma unroll
+        for (int k = 0; k < TOK; ++k) r[k] = (FULL || l0 + k < L) ? rstd[b * L + l0 + k] : 0.0f;
+        slice_sum(s, sm, sl, grp);
+#pragma unroll
+        for (int k = 0; k < TOK; ++k) c[k] = r[k] * r[k] * s[k] / (float)dim;
+        const auto grad = [&](const float (&xv)[TOK], const float (&gv)[TOK], int64_t fb) {      // feature fb + sl
+            const int64_t f = fb + sl;
+            float o[TOK], pw = 0.0f;
+            if (dres) {
+                if constexpr (FULL) load_run<T, TOK, true>(dres + off + fb * L + lane, 0, L, o);
+                else load_run<T, TOK>(dres + off + f * L, l0, L, o);
+            }
+            const float wv = w[f];
+#pragma unroll
+            for (int k = 0; k < TOK; ++k) {
+                const float v = r[k] * (gv[k] * wv - xv[k] * c[k]);
+                o[k] = dres ? o[k] + v : v;
+                pw = fmaf(gv[k] * xv[k], r[k], pw);      // 0 past the row end: loads read 0
+            }
+            if constexpr (FULL) store_run<TO, TOK, true>(dx + off + fb * L + lane, 0, L, o);
+            else store_run<TO, TOK>(dx + off + f * L, l0, L, o);
+            // over the groups of the slice (consecutive lanes), in a fixed order
+#pragma unroll
+            for (int m = 1; m < GROUPS; m *= 2) pw += __shfl_xor(pw, m, GROUPS);
+            if (grp == 0) pb[f] = pw;
+        };
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            float xv[TOK], gv[TOK];
+            unpack_run(xr[i], xv);
+            unpack_run(gr[i], gv);
+            if (sl + i * SL < dim) grad(xv, gv, i * SL);
+        }
+        for (int64_t f = sl + C * SL; f < dim; f += SL) {
+            float xv[TOK], gv[TOK];
+            load_run<T, TOK, FULL>(xb + f * L, l0, L, xv);
+            load_run<T, TOK, FULL>(gb + f * L, l0, L, gv);
+            grad(xv, gv, f - sl);
+        }
+    };
+    if (l0 - grp * TOK + Smem::kTile <= L) body(std::true_type{});
+    else body(std::false_type{});
 }
 
-// dw[f] = sum over the (batch, tile) rows of partial[., f], in a fixed order and in two
-// passes: a single pass with one thread per feature chained 512 loads per thread at the
-// Mamba-1.4B block shape (156 us).  Pass one: block (feature chunk of 64, slab s) sums
-// the rows of its slab, each of 4 waves taking every 4th row, and adds the 4 wave sums
-// in order; pass two adds the slabs in order.
-constexpr int kFinFeat = 64;
-__global__ __launch_bounds__(256) void rmsnorm_bwd_finalize_slabs(const float* __restrict__ partial,
-                                                                 float* __restrict__ slabs, int64_t rows,
-                                                                 int64_t dim) {
-    __shared__ float part[4][kFinFeat];
-    const int fo = threadIdx.x & (kFinFeat - 1), rg = threadIdx.x / kFinFeat;
+// dw[f] = sum over the (batch, tile) rows of partial[., f], in a fixed order: a block owns
+// 32 features (128 bytes of each row), each of its 32 row groups sums every 32nd row, eight
+// loads in flight, and the groups' sums are added in order.  One launch in place of two
+// (slabs, then slabs' sums), 5 us less; a thread per feature chained 512 loads (156 us at
+// the Mamba-1.4B block's shape).
+constexpr int kFinFeat = 32, kFinRows = 32;
+__global__ __launch_bounds__(kFinFeat * kFinRows) void rmsnorm_bwd_finalize(const float* __restrict__ partial,
+                                                                          float* __restrict__ dw, int64_t rows,
+                                                                          int64_t dim) {
+    __shared__ float part[kFinRows][kFinFeat];
+    const int fo = threadIdx.x % kFinFeat, rg = threadIdx.x / kFinFeat;
     const int64_t f = (int64_t)blockIdx.x * kFinFeat + fo;
-    const int64_t per = (rows + kRmsSlabs - 1) / kRmsSlabs;
-    const int64_t i0 = (int64_t)blockIdx.y * per, i1 = min(rows, i0 + per);
     float a = 0.0f;
-    if (f < dim)
-        for (int64_t i = i0 + rg; i < i1; i += 4) a += partial[i * dim + f];
+    if (f < dim) {
+        int64_t i = rg;
+        for (; i + 7 * kFinRows < rows; i += 8 * kFinRows) {
+            float v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = partial[(i + q * kFinRows) * dim + f];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) a += v[q];
+        }
+        for (; i < rows; i += kFinRows) a += partial[i * dim + f];
+    }
     part[rg][fo] = a;
     __syncthreads();
-    if (rg == 0 && f < dim) slabs[blockIdx.y * dim + f] = ((part[0][fo] + part[1][fo]) + part[2][fo]) + part[3][fo];
+    if (rg == 0 && f < dim) {
+#pragma unroll
+        for (int q = 1; q < kFinRows; ++q) a += part[q][fo];
+        dw[f] = a;
+    }
 }
 
-__global__ void rmsnorm_bwd_finalize(const float* __restrict__ slabs, float* __restrict__ dw, int64_t dim) {
-    const int64_t f = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (f >= dim) return;
-    float a = 0.0f;
-#pragma unroll
-    for (int q = 0; q < kRmsSlabs; ++q) a += slabs[q * dim + f];
-    dw[f] = a;
+// 8 groups where tiles of 8 give two blocks for each CU, else 4.
+template <typename T>
+bool wide_tiles(const RmsArgs& a) {
+    constexpr int64_t kTile = 8 * Storage<T>::kPerVec;
+    return a.batch * ((a.seqlen + kTile - 1) / kTile) >= 512;
+}
+
+template <typename T, typename TO, int GROUPS, int THREADS>
+void fwd_g(const RmsArgs& a, hipStream_t s) {
+    constexpr int64_t kTile = GROUPS * Storage<T>::kPerVec;
+    hipLaunchKernelGGL((rmsnorm_fwd_kernel<T, TO, GROUPS, THREADS>),
+                       dim3((unsigned)((a.seqlen + kTile - 1) / kTile), (unsigned)a.batch), dim3(THREADS), 0, s,
+                       static_cast<const T*>(a.x), a.w, a.eps, static_cast<TO*>(a.out), a.rstd_out, a.dim, a.seqlen);
 }
 
 template <typename T, typename TO>
 hipError_t fwd_t(const RmsArgs& a, hipStream_t s) {
-    const dim3 grid((unsigned)((a.seqlen + kTile - 1) / kTile), (unsigned)a.batch);
-    hipLaunchKernelGGL((rmsnorm_fwd_kernel<T, TO>), grid, dim3(kThreads), 0, s, static_cast<const T*>(a.x),
-                       a.w, a.eps, static_cast<TO*>(a.out), a.rstd_out, a.dim, a.seqlen);
+    if (wide_tiles<T>(a)) fwd_g<T, TO, 8, 1024>(a, s);
+    else fwd_g<T, TO, 4, 1024>(a, s);
     return hipGetLastError();
+}
+
+// returns the tiles per row
+template <typename T, typename TO, int GROUPS, int THREADS>
+int64_t bwd_g(const RmsArgs& a, hipStream_t s) {
+    constexpr int64_t kTile = GROUPS * Storage<T>::kPerVec;
+    static_assert(kTile >= kRmsTile, "the workspace holds a partial per kRmsTile tokens");
+    const int64_t row_tiles = (a.seqlen + kTile - 1) / kTile;
+    hipLaunchKernelGGL((rmsnorm_bwd_kernel<T, TO, GROUPS, THREADS>), dim3((unsigned)row_tiles, (unsigned)a.batch),
+                       dim3(THREADS), 0, s, static_cast<const T*>(a.x), a.w, a.rstd, static_cast<const T*>(a.dout),
+                       static_cast<const T*>(a.dres), static_cast<TO*>(a.out), a.partial, a.dim, a.seqlen);
+    return row_tiles;
 }
 
 template <typename T, typename TO>
 hipError_t bwd_t(const RmsArgs& a, hipStream_t s) {
-    const int64_t tiles = (a.seqlen + kTile - 1) / kTile;
-    const dim3 grid((unsigned)tiles, (unsigned)a.batch);
-    hipLaunchKernelGGL((rmsnorm_bwd_kernel<T, TO>), grid, dim3(kThreads), 0, s, static_cast<const T*>(a.x),
-                       a.w, a.rstd, static_cast<const T*>(a.dout), static_cast<const T*>(a.dres),
-                       static_cast<TO*>(a.out), a.partial, a.dim, a.seqlen);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    float* slabs = a.partial + a.batch * tiles * a.dim;
-    hipLaunchKernelGGL(rmsnorm_bwd_finalize_slabs, dim3((unsigned)((a.dim + kFinFeat - 1) / kFinFeat), kRmsSlabs),
-                       dim3(256), 0, s, a.partial, slabs, a.batch * tiles, a.dim);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(rmsnorm_bwd_finalize, dim3((unsigned)((a.dim + 255) / 256)), dim3(256), 0, s,
-                       slabs, a.dw, a.dim);
+    const int64_t rows = a.batch * (wide_tiles<T>(a) ? bwd_g<T, TO, 8, 512>(a, s) : bwd_g<T, TO, 4, 1024>(a, s));
+    if (hipError_t e = hipGetLastError()) return e;
+    hipLaunchKernelGGL(rmsnorm_bwd_finalize, dim3((unsigned)((a.dim + kFinFeat - 1) / kFinFeat)),
+                       dim3(kFinFeat * kFinRows), 0, s, a.partial, a.dw, rows, a.dim);
     return hipGetLastError();
 }
 
