@@ -16,6 +16,12 @@ namespace {
 constexpr int kTok = 8;        // the halo vector of the backward
 constexpr int kTokBwd = 8;     // tokens per thread per step (backward)
 constexpr int kThreads = 256;
+// Waves of one channel that the backward gathers in one block, and the elements up to which
+// it does: the block sums the parameter gradients and saves the finalize's launch (3 us of
+// 37 at 4 x 2048 x 1536, 2.5 of 58 at 2 x 8192 x 2048), but its waves read batch rows far apart
+// at the same time, which costs the large shapes more (187 -> 250 us at 8 x 4096 x 4096).
+constexpr int64_t kConvBwdGather = (int64_t)1 << 25;
+constexpr int kConvBwdParts = 16;
 
 // N position indices from l0 (N a multiple of 4); beyond L they read 0.  FULL: the
 // caller guarantees l0 + N <= L
@@ -63,8 +69,8 @@ __device__ __forceinline__ void load_row_halo(const T* __restrict__ xinit, int64
 // position indices are read and their tap masks compared once for the R, and R vectors
 // per lane are in flight.  The W-1 tokens before a lane's come from the lane before it by
 // a lane shift, only lane 0 of a later tile reads them from memory: a pass reads x once
-// and writes out once.  Bound by HBM at long rows (8 x 4096 x 4096: fp32 207 us, 5.2 TB/s,
-// against 222 us with a block per row and the halo read again; bf16 117 us both ways);
+// and writes out once.  Bound by HBM at long rows (8 x 4096 x 4096: fp32 191 us, 5.6 TB/s,
+// against 233 us with a block per row and the halo read again; bf16 105 against 99);
 // one token of 64 x 4096 channels takes 5.3 us against 177 us with a block per row.
 template <typename T, typename TO, int W, int R>
 __global__ __launch_bounds__(kThreads) void conv1d_fwd_kernel(
@@ -179,16 +185,22 @@ __global__ __launch_bounds__(kThreads) void conv1d_fwd_kernel(
 // are carried.
 // DXF: a final-input gradient is given (a separate instantiation, so that the
 // common path keeps its register count).
-template <typename T, typename TO, int W, int KT, bool DXF>
-__global__ __launch_bounds__(64) void conv1d_bwd_kernel(
+// ALL: a block holds all waves of one channel, batch row by batch row and segment by segment
+// (up to kConvBwdParts of them), and sums their parameter gradients in that order itself;
+// without it a block is one wave, which leaves its part in `partial` for the finalize.
+template <typename T, typename TO, int W, int KT, bool DXF, bool ALL>
+__global__ __launch_bounds__(ALL ? 64 * kConvBwdParts : 64) void conv1d_bwd_kernel(
     const T* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias,
     const int32_t* __restrict__ pos, const T* __restrict__ dout, TO* __restrict__ dx,
-    float* __restrict__ partial, ConvStates<T, TO> st, int64_t dim, int64_t L, int silu) {
+    float* __restrict__ partial, float* __restrict__ dw, float* __restrict__ dbias, ConvStates<T, TO> st,
+    int64_t dim, int64_t L, int nseg, int silu) {
     static_assert(KT >= W - 1 && KT % 4 == 0, "the halo lies in the next lane's tokens");
-    const int64_t row = blockIdx.x;
-    const int64_t b = row / dim, d = row - b * dim;
-    const int seg = blockIdx.y, nseg = gridDim.y;
-    const int lane = (int)threadIdx.x;
+    const int wave = ALL ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+    const int64_t b = ALL ? wave / nseg : blockIdx.x / dim;
+    const int64_t d = ALL ? blockIdx.x : blockIdx.x - b * dim;
+    const int seg = ALL ? wave - (int)b * nseg : blockIdx.y;
+    const int64_t row = b * dim + d;
+    const int lane = (int)(threadIdx.x & 63);
     const T* xr = x + row * L;
     const T* gr = dout + row * L;
     TO* dxr = dx + row * L;
@@ -331,7 +343,21 @@ __global__ __launch_bounds__(64) void conv1d_bwd_kernel(
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) acc[j] += __shfl_xor(acc[j], off, 64);
     }
-    if (lane == 0) {
+    if constexpr (ALL) {
+        __shared__ float part[kConvBwdParts][W + 1];
+        if (lane == 0) {
+#pragma unroll
+            for (int j = 0; j <= W; ++j) part[wave][j] = acc[j];
+        }
+        __syncthreads();
+        if (threadIdx.x <= W) {
+            const int j = (int)threadIdx.x, parts = (int)(blockDim.x >> 6);
+            float s = 0.0f;
+            for (int r = 0; r < parts; ++r) s += part[r][j];
+            if (j < W) dw[d * W + j] = s;
+            else if (dbias) dbias[d] = s;
+        }
+    } else if (lane == 0) {
         float* pp = partial + ((b * nseg + seg) * dim + d) * (W + 1);
 #pragma unroll
         for (int j = 0; j <= W; ++j) pp[j] = acc[j];
@@ -352,8 +378,9 @@ __global__ void conv1d_bwd_finalize(const float* __restrict__ partial, float* __
     else if (dbias) dbias[d] = s;
 }
 
-// Rows per lane of the forward: 4 when that leaves 8 waves for each of the 1024 SIMDs.
-constexpr int kFwdRows = 4;
+// Rows per lane of the forward: 2 when that leaves 8 waves for each of the 1024 SIMDs (1, 2, 4
+// and 8 rows at 8 x 4096 x 4096: 113, 105, 105, 131 us in bf16, 229, 191, 206, 249 in fp32).
+constexpr int kFwdRows = 2;
 constexpr int64_t kFwdWaves = 8192;
 
 template <typename T, typename TO, int W>
@@ -390,32 +417,38 @@ hipError_t conv_fwd_t(const ConvArgs& a, hipStream_t s) {
 }
 
 template <typename T, typename TO, int W, bool DXF>
-void conv_bwd_w(const ConvArgs& a, hipStream_t s) {
+hipError_t conv_bwd_w(const ConvArgs& a, hipStream_t s) {
     const ConvStates<T, TO> st{static_cast<const T*>(a.xinit), nullptr, static_cast<const T*>(a.dxfinal),
                                static_cast<TO*>(a.dxinit)};
-    const unsigned nseg = (unsigned)conv_bwd_segments(a.batch, a.dim, a.seqlen);
-    hipLaunchKernelGGL((conv1d_bwd_kernel<T, TO, W, kTokBwd, DXF>), dim3((unsigned)(a.batch * a.dim), nseg),
-                       dim3(64), 0, s, static_cast<const T*>(a.x), a.w, a.bias, a.pos,
-                       static_cast<const T*>(a.dout), static_cast<TO*>(a.out), a.partial, st, a.dim,
-                       a.seqlen, a.silu);
+    const T* x = static_cast<const T*>(a.x);
+    const T* g = static_cast<const T*>(a.dout);
+    TO* dx = static_cast<TO*>(a.out);
+    const int64_t nseg = conv_bwd_segments(a.batch, a.dim, a.seqlen), parts = a.batch * nseg;
+    if (parts <= kConvBwdParts && a.batch * a.dim * a.seqlen <= kConvBwdGather) {
+        hipLaunchKernelGGL((conv1d_bwd_kernel<T, TO, W, kTokBwd, DXF, true>), dim3((unsigned)a.dim),
+                           dim3((unsigned)(64 * parts)), 0, s, x, a.w, a.bias, a.pos, g, dx, a.partial, a.dw, a.dbias,
+                           st, a.dim, a.seqlen, (int)nseg, a.silu);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL((conv1d_bwd_kernel<T, TO, W, kTokBwd, DXF, false>),
+                       dim3((unsigned)(a.batch * a.dim), (unsigned)nseg), dim3(64), 0, s, x, a.w, a.bias, a.pos, g, dx,
+                       a.partial, a.dw, a.dbias, st, a.dim, a.seqlen, (int)nseg, a.silu);
+    if (hipError_t e = hipGetLastError()) return e;
+    // the partials of every (batch row, segment) are summed like batch rows
+    const int64_t n = a.dim * (a.width + 1);
+    hipLaunchKernelGGL(conv1d_bwd_finalize, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                       a.partial, a.dw, a.dbias, parts, a.dim, (int)a.width);
+    return hipGetLastError();
 }
 
 template <typename T, typename TO>
 hipError_t conv_bwd_t(const ConvArgs& a, hipStream_t s) {
     const bool dxf = a.dxfinal != nullptr;
     switch (a.width) {
-        case 2: dxf ? conv_bwd_w<T, TO, 2, true>(a, s) : conv_bwd_w<T, TO, 2, false>(a, s); break;
-        case 3: dxf ? conv_bwd_w<T, TO, 3, true>(a, s) : conv_bwd_w<T, TO, 3, false>(a, s); break;
-        default: dxf ? conv_bwd_w<T, TO, 4, true>(a, s) : conv_bwd_w<T, TO, 4, false>(a, s); break;
+        case 2: return dxf ? conv_bwd_w<T, TO, 2, true>(a, s) : conv_bwd_w<T, TO, 2, false>(a, s);
+        case 3: return dxf ? conv_bwd_w<T, TO, 3, true>(a, s) : conv_bwd_w<T, TO, 3, false>(a, s);
+        default: return dxf ? conv_bwd_w<T, TO, 4, true>(a, s) : conv_bwd_w<T, TO, 4, false>(a, s);
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    // the partials of every (batch row, segment) are summed like batch rows
-    const int64_t n = a.dim * (a.width + 1);
-    hipLaunchKernelGGL(conv1d_bwd_finalize, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                       a.partial, a.dw, a.dbias, a.batch * conv_bwd_segments(a.batch, a.dim, a.seqlen),
-                       a.dim, (int)a.width);
-    return hipGetLastError();
 }
 
 }  // namespace

@@ -50,7 +50,7 @@ def test_scan_forward_short_rows(shape, states, dtype):
 
 # tokens around one lane's vector (4 and 8), around the powers of two of lanes per row, a wave's
 # span (256 and 512) and more tiles; channels that leave a wave's rows ragged.  The last shapes
-# have enough rows for four per lane: 64 rows a wave, and one row in two tiles.
+# have enough rows for several per lane: 64 rows a wave, and one row in two tiles.
 CONV_SHAPES = [(1, 1, 1), (2, 70, 2), (3, 33, 5), (2, 5, 8), (2, 17, 9), (1, 9, 31), (2, 3, 255), (1, 6, 257),
                (2, 3, 512), (1, 5, 513), (1, 2, 1541), (64, 33000, 1), (130, 131, 513)]
 
@@ -82,3 +82,25 @@ def test_conv_forward_lanes_and_tiles(shape, width, dtype):
     assert np.array_equal(host(fin), np.asarray(rfin, dtype=np.float64))
     plain = P.causal_conv1d_fwd(act(x, dtype), f32(w), None, i32(pos), silu=False, out_f32=dtype == "bf16")
     assert_close("plain", host(plain), O.conv1d_fwd(x, w, None, pos, silu=False), TOL["f32"])
+
+
+# waves per channel that one block gathers: 1, 3, 16 (4 rows of 4 segments), and one wave per
+# block beyond 16 (17 batch rows) or beyond the size limit (the last shape)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(1, 3, 70), (3, 5, 1030), (4, 6, 2049), (17, 4, 30), (4, 4100, 2050)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_conv_backward_gathered_waves(shape, dtype):
+    import oracle as O
+    import paper_2408_03865_amd as P
+    batch, dim, L = shape
+    rng = np.random.default_rng(batch * 7 + dim + L)
+    rnd = W.bf16_round if dtype == "bf16" else (lambda a: a)
+    x, g = (rnd(rng.standard_normal((batch, dim, L)).astype(np.float32)) for _ in range(2))
+    w = rng.uniform(-0.5, 0.5, (dim, 4)).astype(np.float32)
+    bias = rng.uniform(-0.5, 0.5, dim).astype(np.float32)
+    pos = W.positions_from_lengths(W.draw_row_lengths(("lognormal", 4.0, 1.0, 1, L), rng, batch, L), L)
+    note(f"conv bwd {shape} {dtype}")
+    dx, dw, db = P.causal_conv1d_bwd(act(x, dtype), f32(w), f32(bias), i32(pos), act(g, dtype), out_f32=dtype == "bf16")
+    ref = O.conv1d_bwd(x, w, bias, pos, g)
+    for k, got in (("dx", dx), ("dw", dw), ("dbias", db)):
+        assert_close(k, host(got), ref[k], TOL["f32"])
