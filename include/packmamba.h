@@ -191,7 +191,8 @@ size_t packmamba_selective_scan_fwd_workspace_size(int64_t batch, int64_t dim, i
  *   The backward reuses both instead of recomputing them.
  *   `out` may be NULL when saved_states or final_state is not (states only).
  *   initial_state: NULL (zeros), or (batch, dim, dstate) float: h before each row.
- *   final_state: NULL, or (batch, dim, dstate) float, receives h after each row.
+ *   final_state: NULL, or (batch, dim, dstate) float, receives h after each row; it may
+ *   be initial_state's buffer (states updated in place).
  *   workspace: device scratch of packmamba_selective_scan_fwd_workspace_size()
  *   bytes, owned by the caller and not read after the call's kernels finish; may
  *   be NULL when that size is 0.  Too small or missing: PACKMAMBA_ERR_WORKSPACE.
@@ -224,7 +225,8 @@ size_t packmamba_selective_scan_bwd_workspace_size(int64_t batch, int64_t dim, i
  *   Outputs (overwritten): du, ddelta (dtype, like u); dA (dim, dstate);
  *   dB, dC (batch, dstate, seqlen) float; dD (dim) iff D != NULL;
  *   dz (dtype) iff z != NULL; ddelta_bias (dim) iff delta_bias != NULL;
- *   dinitial_state (batch, dim, dstate) float iff initial_state != NULL.
+ *   dinitial_state (batch, dim, dstate) float iff initial_state != NULL; it may be
+ *   dfinal_state's buffer.
  *   Sums over channels and tokens use per-block partials in the workspace and a
  *   second pass in fixed order: results are bitwise reproducible.
  */

@@ -36,13 +36,19 @@ int64_t state_chunks(int64_t seqlen) {
     return (seqlen + PACKMAMBA_STATE_STRIDE - 1) / PACKMAMBA_STATE_STRIDE;
 }
 
-// Segment split workspace, shared by both directions: the per-segment maps
-// (batch, dim, nseg, kN, 2), and a third float for each that no kernel uses: the size that
+// Segment split workspace, shared by both directions: what enters each row (batch, dim, kN),
+// then the per-segment maps (batch, dim, nseg, kN, 2).  Three floats for each (channel,
+// state, segment), where the copies need one for each (channel, state): the size that
 // callers were told stays what it was when the chained carries were stored.  Empty when
 // the rows are not split.
 size_t seg_ws(int64_t batch, int64_t dim, const pm::SegPlan& sp) {
     const size_t maps = sizeof(float) * (size_t)(batch * dim * sp.nseg * kN);
     return sp.nseg > 1 ? align_up(2 * maps) + align_up(maps) : 0;
+}
+
+void set_seg_ws(pm::ScanArgs& a, void* base, int64_t batch, int64_t dim) {
+    a.ws_entry = static_cast<float*>(base);
+    a.ws_agg = a.ws_entry + align_up(sizeof(float) * (size_t)(batch * dim * kN)) / sizeof(float);
 }
 
 // Saved states of the forward: the chunk states (batch, dim, chunk, dstate), then the
@@ -215,7 +221,7 @@ int packmamba_selective_scan_fwd(const void* u, const void* delta, const float* 
     const size_t need = seg_ws(batch, dim, pm::scan_fwd_plan(batch, dim, seqlen).seg);
     if (need && (!workspace || workspace_bytes < need)) return PACKMAMBA_ERR_WORKSPACE;
     pm::ScanArgs a{};
-    a.ws_agg = static_cast<float*>(workspace);
+    if (need) set_seg_ws(a, workspace, batch, dim);
     a.u = u; a.delta = delta; a.A = A; a.B = B; a.C = C; a.D = D; a.z = z;
     a.delta_bias = delta_bias; a.pos = position_indices; a.softplus = delta_softplus ? 1 : 0;
     a.out = out; a.states = saved_states; a.h0 = initial_state; a.hfinal = final_state;
@@ -268,7 +274,7 @@ int packmamba_selective_scan_bwd(const void* u, const void* delta, const float* 
     hipStream_t s = (hipStream_t)stream;
     // the forward recompute below and the backward run one after the other on the
     // stream, so they share the segment workspace
-    a.ws_agg = reinterpret_cast<float*>(ws + w.part_bc + w.part_chan + w.states);
+    set_seg_ws(a, ws + w.part_bc + w.part_chan + w.states, batch, dim);
     char* saved = saved_states ? reinterpret_cast<char*>(const_cast<float*>(saved_states))
                                : ws + w.part_bc + w.part_chan;
     a.states = reinterpret_cast<float*>(saved);

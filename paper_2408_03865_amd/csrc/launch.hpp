@@ -109,7 +109,8 @@ struct ScanArgs {
     float* ddelta_bias;
     float* part_bc;         // (batch, groups, 2, dstate, seqlen)
     float* part_chan;       // (batch, nseg, dim, dstate + 2)
-    // segment split (both directions): per-segment maps
+    // segment split (both directions): what enters each row, copied, and per-segment maps
+    float* ws_entry;        // (batch, dim, dstate)
     float* ws_agg;          // (batch, dim, nseg, dstate, 2)
     int64_t batch, dim, seqlen;
     int32_t dstate, dtype;

@@ -71,8 +71,10 @@ struct BwdParams {
     const float* states;
     const float* dzf;     // (batch, dim, L): factor of dout in dz, saved by the forward
     const float* h0;      // state before each row (batch, dim, kN), or null
-    const float* dhfinal; // gradient of the state after each row, or null
-    float* dh0;           // gradient of h0, or null
+    const float* dhfinal; // gradient of the state after each row, or null; the main pass of split
+                          // rows reads `entry`
+    float* entry;         // split rows: copy of dhfinal, by the aggregate pass
+    float* dh0;           // gradient of h0, or null; may be dhfinal's buffer
     void* du;
     void* ddelta;
     void* dz;
@@ -506,6 +508,9 @@ __global__ __launch_bounds__(kThreads) void scan_bwd_agg_kernel(BwdParams p) {
         sm.A2[rr][n] = p.A[dd * kN + n] * kLog2e;
         sm.xc[rr][n] = 0.0f;
         sm.q[rr][n] = 1.0f;
+        // The main pass's blocks each start from dhfinal, and the first segment's write dh0,
+        // which may be the same memory.
+        if (seg == 1 && p.dhfinal) p.entry[(b * p.dim + dd) * kN + n] = p.dhfinal[(b * p.dim + dd) * kN + n];
     }
 
     auto chunk = [&](auto full_tag, const int64_t c) {
@@ -676,12 +681,14 @@ hipError_t launch_t(const ScanArgs& a, hipStream_t s) {
     static_assert(kSegUnit % kCH == 0, "segments hold whole chunks");
     p.seg_chunks = sp.seg_len / kCH;
     p.nseg = (int)sp.nseg;
+    p.entry = a.ws_entry;
     p.agg = reinterpret_cast<float2*>(a.ws_agg);
     const dim3 groups((unsigned)p.groups, (unsigned)a.batch);
     if (sp.nseg > 1) {
         hipLaunchKernelGGL((scan_bwd_agg_kernel<T>), dim3(groups.x, groups.y, (unsigned)(sp.nseg - 1)), dim3(kThreads),
                            0, s, p);
         if (hipError_t e = hipGetLastError()) return e;
+        if (p.dhfinal) p.dhfinal = p.entry;
     }
     hipLaunchKernelGGL((scan_bwd_kernel<T, TO>), dim3(groups.x, groups.y, (unsigned)sp.nseg), dim3(kThreads), 0, s, p);
     if (hipError_t e = hipGetLastError()) return e;

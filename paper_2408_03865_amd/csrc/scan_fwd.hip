@@ -65,8 +65,10 @@ struct FwdParams {
     void* out;
     float* states;
     float* dzf;               // (batch, dim, L): factor of dout in dz, or null
-    const float* h0;          // state before each row (batch, dim, kN), or null
-    float* hfinal;            // state after each row (batch, dim, kN), or null
+    const float* h0;          // state before each row (batch, dim, kN), or null; the main pass of
+                              // split rows reads `entry`
+    float* entry;             // split rows: copy of h0, by the aggregate pass
+    float* hfinal;            // state after each row (batch, dim, kN), or null; may be h0's buffer
     float2* agg;              // the segments' maps (batch, dim, nseg, kN) = (P, H): written by the
                               // aggregate pass, chained by the main pass
     int64_t dim, L;
@@ -131,6 +133,10 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
         if (!AGG) {
             if (p.h0) c0v = p.h0[(b * p.dim + dd) * kN + n];
             c0v = chain_maps(p.agg + (b * p.dim + dd) * p.nseg * kN + n, seg, c0v);
+        } else if (seg == 0 && p.h0) {
+            // The main pass's blocks each start from h0, and the last segment's write hfinal,
+            // which may be the same memory (a serving loop that updates its states in place).
+            p.entry[(b * p.dim + dd) * kN + n] = p.h0[(b * p.dim + dd) * kN + n];
         }
         sm.carry[rr][n] = c0v;
         sm.pseg[rr][n] = 1.0f;
@@ -428,7 +434,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_short_kernel(FwdParams p) {
 constexpr int kAggLanes = 32;
 
 template <typename T, typename TO, int LANES>
-hipError_t launch_lanes(const ScanArgs& a, const FwdParams& p, hipStream_t s) {
+hipError_t launch_lanes(const ScanArgs& a, FwdParams p, hipStream_t s) {
     constexpr int kRows = FwdSmem<LANES>::kRows;
     const dim3 grid((unsigned)((a.dim + kRows - 1) / kRows), (unsigned)a.batch, (unsigned)p.nseg);
     if (p.nseg > 1) {
@@ -437,6 +443,7 @@ hipError_t launch_lanes(const ScanArgs& a, const FwdParams& p, hipStream_t s) {
         hipLaunchKernelGGL((scan_fwd_kernel<T, TO, kAggLanes, true>),
                            dim3((unsigned)((a.dim + kAggRows - 1) / kAggRows), grid.y, grid.z - 1), dim3(kThreads), 0, s, p);
         if (hipError_t e = hipGetLastError()) return e;
+        if (p.h0) p.h0 = p.entry;
     }
     hipLaunchKernelGGL((scan_fwd_kernel<T, TO, LANES, false>), grid, dim3(kThreads), 0, s, p);
     return hipGetLastError();
@@ -463,6 +470,7 @@ hipError_t launch_t(const ScanArgs& a, hipStream_t s) {
     static_assert(kSegUnit % kCH == 0, "segments hold whole chunks");
     p.seg_chunks = sp.seg_len / kCH;
     p.nseg = (int)sp.nseg;
+    p.entry = a.ws_entry;
     p.agg = reinterpret_cast<float2*>(a.ws_agg);
     switch (plan.lanes) {
         case 64: return launch_lanes<T, TO, 64>(a, p, s);
