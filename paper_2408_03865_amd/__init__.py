@@ -78,9 +78,11 @@ def _p(t) -> Optional[int]:
 
 def _stream(t) -> int:
     torch = _torch()
-    if t.is_cuda:
-        return torch._C._cuda_getCurrentRawStream(t.get_device())
-    return torch.cuda.current_stream(t.device).cuda_stream      # raises: not on a GPU
+    # the number without a Stream object around it, where this build of torch gives it
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is not None and t.is_cuda:
+        return raw(t.get_device())
+    return torch.cuda.current_stream(t.device).cuda_stream      # raises if t is not on a GPU
 
 
 @functools.lru_cache(maxsize=256)

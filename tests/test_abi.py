@@ -218,3 +218,13 @@ def test_load_follows_lib_path(tmp_path):
     finally:
         L.LIB_PATH = old
     assert L.load()._name == old
+
+
+def test_stream_without_the_raw_getter(monkeypatch):
+    """A torch build that lacks the raw stream getter gives the stream through its public API."""
+    from types import SimpleNamespace
+    import torch
+    import paper_2408_03865_amd as P
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda dev: SimpleNamespace(cuda_stream=1000 + dev))
+    assert P._stream(SimpleNamespace(is_cuda=True, device=3, get_device=lambda: 3)) == 1003
