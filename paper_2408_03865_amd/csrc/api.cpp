@@ -307,7 +307,9 @@ int packmamba_rmsnorm_fwd(const void* x, const float* weight, float eps, void* o
 size_t packmamba_rmsnorm_bwd_workspace_size(int64_t batch, int64_t dim, int64_t seqlen) {
     if (check_shape(batch, dim, seqlen)) return 0;
     const int64_t tiles = (seqlen + pm::kRmsTile - 1) / pm::kRmsTile;
-    return align_up(sizeof(float) * (size_t)(batch * tiles * dim));
+    // the partials and 16 rows that no kernel uses: the size that callers were told stays what
+    // it was when the partials were summed in two passes
+    return align_up(sizeof(float) * (size_t)((batch * tiles + 16) * dim));
 }
 
 int packmamba_rmsnorm_bwd(const void* x, const float* weight, const float* rstd, const void* dout,

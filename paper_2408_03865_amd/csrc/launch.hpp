@@ -43,7 +43,7 @@ int conv1d_bwd_noalloc_status(const void* x, const float* weight, const float* b
 hipError_t launch_conv1d_bwd(const ConvArgs& a, hipStream_t s);
 
 // RMSNorm over the feature axis of (batch, dim, seqlen) activations.
-constexpr int64_t kRmsTile = 16;     // fewest tokens per block of the backward; one dweight partial per (batch, tile)
+constexpr int64_t kRmsTile = 64;     // tokens per block of the backward; one dweight partial per (batch, tile)
 struct RmsArgs {
     const void* x;
     const float* w;

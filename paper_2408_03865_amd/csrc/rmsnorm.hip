@@ -6,28 +6,23 @@
 // A block owns a tile of consecutive tokens of one batch row: GROUPS lanes side by side,
 // each with one 16-byte vector of tokens, so that every feature row gives GROUPS x 16
 // contiguous bytes, and THREADS / GROUPS slices of the features.  A thread keeps the
-// vectors of its first kKept features in registers from the sum over the features to the
+// vectors of its first KEPT features in registers from the sum over the features to the
 // second sweep; features beyond those are read again.
 // Bound by HBM where there are tiles enough for the GPU.  Us, forward and backward, against
 // 1024 threads that keep nothing and 8 tokens per lane in both types:
-//   8 x 4096 x 2048 bf16 (67 M elements)  60, 154   before 71, 173
-//   8 x 4096 x 2048 fp32                 108, 295   before 178, 356
-//   2 x 3001 x 2560 bf16                  55,  89   before 143, 284
-// 64-byte rows of a tile (4 groups) make up for few tiles, but cost the large shapes their
-// HBM pages (backward 240 us at the first of these), so they are used below 512 tiles.
+//   8 x 4096 x 2048 bf16 (67 M elements)  49, 133   before 60, 165
+//   8 x 4096 x 2048 fp32                  96, 257   before 166, 349
+//   2 x 3001 x 2560 bf16                  44,  87   before 134, 273
 #include "common.hpp"
 #include "launch.hpp"
 
 namespace pm {
 namespace {
 
-// Features a thread keeps in registers (64 VGPRs of x and dh in the backward; with 16 the
-// forward spilled at 1024 threads: 172 us against 62 at 8 x 4096 x 2048).
-constexpr int kKept = 8;
+constexpr int64_t kCus = 256;
 
-// (batch row) x (tiles per row) + tile of this block.  Blocks go to the 8 XCDs in turn; with
-// 64-byte rows of a tile, the two tiles that share 128-byte lines go to the same one
-// (2 x 3001 x 2560 bf16: backward 89 us against 102).
+// Forward: (batch row) x (tiles per row) + tile of this block.  Blocks go to the 8 XCDs in
+// turn; with 64-byte rows of a tile, the two tiles that share 128-byte lines go to the same one.
 template <int GROUPS>
 __device__ __forceinline__ int64_t tile_id() {
     const int64_t id = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
@@ -75,7 +70,7 @@ __device__ __forceinline__ void slice_sum(float (&v)[TOK], RmsSmem<GROUPS, THREA
     }
 }
 
-template <typename T, typename TO, int GROUPS, int THREADS>
+template <typename T, typename TO, int GROUPS, int THREADS, int KEPT>
 __global__ __launch_bounds__(THREADS) void rmsnorm_fwd_kernel(const T* __restrict__ x, const float* __restrict__ w,
                                                               float eps, TO* __restrict__ out,
                                                               float* __restrict__ rstd, int64_t dim, int64_t L) {
@@ -86,15 +81,19 @@ __global__ __launch_bounds__(THREADS) void rmsnorm_fwd_kernel(const T* __restric
     const int grp = threadIdx.x % GROUPS, sl = threadIdx.x / GROUPS;
     const int64_t id = tile_id<GROUPS>();
     const int64_t b = id / gridDim.x;
-    const int64_t l0 = (id - b * gridDim.x) * Smem::kTile + grp * TOK;
+    const int64_t t0 = (id - b * gridDim.x) * Smem::kTile;
+    const bool whole = t0 + Smem::kTile <= L || L % TOK == 0;      // no vector crosses the row end
+    const bool live = t0 + grp * TOK < L;
+    const int64_t l0 = whole && !live ? t0 : t0 + grp * TOK;
     const T* xb = x + b * dim * L;
     TO* ob = out + b * dim * L;
-    // FULL (block-uniform): the tile lies inside the row
+    // FULL (block-uniform): no vector crosses the row end; lanes past it repeat the tile's
+    // first and store nothing
     const auto body = [&](auto full_tag) {
         constexpr bool FULL = decltype(full_tag)::value;
-        constexpr int C = FULL ? kKept : 0;                     // features kept in registers
+        constexpr int C = FULL ? KEPT : 0;                      // features kept in registers
         const int64_t lane = sl * L + l0;                    // this lane's vector of feature sl
-        RawRun<T, TOK> xr[kKept];
+        RawRun<T, TOK> xr[KEPT];
 #pragma unroll
         for (int i = 0; i < C; ++i) {
             xr[i] = RawRun<T, TOK>{};
@@ -123,14 +122,14 @@ __global__ __launch_bounds__(THREADS) void rmsnorm_fwd_kernel(const T* __restric
         if (sl == 0) {
 #pragma unroll
             for (int k = 0; k < TOK; ++k)
-                if (FULL || l0 + k < L) rstd[b * L + l0 + k] = r[k];
+                if (FULL ? live : l0 + k < L) rstd[b * L + l0 + k] = r[k];
         }
         const auto scale = [&](float (&v)[TOK], int64_t fb) {      // feature fb + sl
             const int64_t f = fb + sl;
             const float wv = w[f];
 #pragma unroll
             for (int k = 0; k < TOK; ++k) v[k] = v[k] * r[k] * wv;
-            if constexpr (FULL) store_run<TO, TOK, true>(ob + fb * L + lane, 0, L, v);
+            if constexpr (FULL) { if (live) store_run<TO, TOK, true>(ob + fb * L + lane, 0, L, v); }
             else store_run<TO, TOK>(ob + f * L, l0, L, v);
         };
 #pragma unroll
@@ -145,41 +144,56 @@ __global__ __launch_bounds__(THREADS) void rmsnorm_fwd_kernel(const T* __restric
             scale(v, f - sl);
         }
     };
-    if (l0 - grp * TOK + Smem::kTile <= L) body(std::true_type{});
+    if (whole) body(std::true_type{});
     else body(std::false_type{});
 }
 
 // dx = r (dh w - x r^2 s / dim) (+ dres), s = sum_f dh w x at each token;
 // partial[b, tile, f] = sum over the tile's tokens of dh x r.
-template <typename T, typename TO, int GROUPS, int THREADS>
+// A tile is 64 tokens: one partial row per 64 tokens is what the workspace holds, whatever the
+// launch.  Where that leaves CUs idle, gridDim.z blocks (a power of two) share a tile: each
+// sums over all features and writes the gradients of its part of them, every gridDim.z-th of
+// a slice's.  The sum's loads are repeated, from the XCD's L2 that the blocks of a tile share.
+template <typename T, typename TO, int THREADS, int KEPT>
 __global__ __launch_bounds__(THREADS) void rmsnorm_bwd_kernel(
     const T* __restrict__ x, const float* __restrict__ w, const float* __restrict__ rstd,
     const T* __restrict__ dh, const T* __restrict__ dres, TO* __restrict__ dx,
     float* __restrict__ partial, int64_t dim, int64_t L) {
-    constexpr int TOK = Storage<T>::kPerVec;
+    constexpr int TOK = Storage<T>::kPerVec, GROUPS = kRmsTile / TOK;
     using Smem = RmsSmem<GROUPS, THREADS, TOK>;
     constexpr int SL = Smem::kSlices;
     __shared__ Smem sm;
     const int grp = threadIdx.x % GROUPS, sl = threadIdx.x / GROUPS;
-    const int64_t id = tile_id<GROUPS>();
+    // blocks go to the 8 XCDs in turn: the parts of a tile are 8 blocks apart
+    const int64_t tiles = (int64_t)gridDim.x * gridDim.y;
+    const int64_t blk = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+    const int parts = (int)gridDim.z, parts_log2 = __builtin_ctz(gridDim.z);
+    const int64_t first = blk / (8 * parts) * 8;
+    const int in = (int)(blk - first * parts), wide = (int)min(tiles - first, (int64_t)8);
+    const int64_t id = first + in % wide;
+    const int part = in / wide;
     const int64_t b = id / gridDim.x;
-    const int64_t l0 = (id - b * gridDim.x) * Smem::kTile + grp * TOK;
+    const int64_t t0 = (id - b * gridDim.x) * Smem::kTile;
+    const bool whole = t0 + Smem::kTile <= L || L % TOK == 0;      // as in the forward
+    const bool live = t0 + grp * TOK < L;
+    const int64_t l0 = whole && !live ? t0 : t0 + grp * TOK;
     const int64_t off = b * dim * L;
     const T* xb = x + off;
     const T* gb = dh + off;
     float* pb = partial + id * dim;
-    // FULL (block-uniform): the tile lies inside the row
     const auto body = [&](auto full_tag) {
         constexpr bool FULL = decltype(full_tag)::value;
-        constexpr int C = FULL ? kKept : 0;                     // features kept in registers
+        constexpr int C = FULL ? KEPT : 0;                      // features kept in registers
         const int64_t lane = sl * L + l0;                    // this lane's vector of feature sl
-        RawRun<T, TOK> xr[kKept], gr[kKept];
+        const int64_t own = (int64_t)part * SL, step = (int64_t)parts * SL;   // the block's features: sl + own + i step
+        RawRun<T, TOK> xr[KEPT], gr[KEPT];
 #pragma unroll
         for (int i = 0; i < C; ++i) {
             xr[i] = gr[i] = RawRun<T, TOK>{};
-            if (sl + i * SL < dim) {
-                xr[i] = load_raw<T, TOK>(xb + i * SL * L + lane, 0);
-                gr[i] = load_raw<T, TOK>(gb + i * SL * L + lane, 0);
+            const int64_t fb = own + i * step;
+            if (sl + fb < dim) {
+                xr[i] = load_raw<T, TOK>(xb + fb * L + lane, 0);
+                gr[i] = load_raw<T, TOK>(gb + fb * L + lane, 0);
             }
         }
         float s[TOK] = {};
@@ -192,13 +206,21 @@ __global__ __launch_bounds__(THREADS) void rmsnorm_bwd_kernel(
             float xv[TOK], gv[TOK];
             unpack_run(xr[i], xv);
             unpack_run(gr[i], gv);
-            if (sl + i * SL < dim) dot(xv, gv, w[sl + i * SL]);
+            const int64_t f = sl + own + i * step;
+            if (f < dim) dot(xv, gv, w[f]);
         }
-        for (int64_t f = sl + C * SL; f < dim; f += SL) {
+        const auto sweep = [&](int64_t f) {
             float xv[TOK], gv[TOK];
             load_run<T, TOK, FULL>(xb + f * L, l0, L, xv);
             load_run<T, TOK, FULL>(gb + f * L, l0, L, gv);
             dot(xv, gv, w[f]);
+        };
+        if (parts == 1) {
+            for (int64_t f = sl + C * SL; f < dim; f += SL) sweep(f);
+        } else {
+            int i = 0;
+            for (int64_t f = sl; f < dim; f += SL, ++i)
+                if ((i & (parts - 1)) != part || (i >> parts_log2) >= C) sweep(f);
         }
         float r[TOK], c[TOK];
 #pragma unroll
@@ -220,7 +242,8 @@ __global__ __launch_bounds__(THREADS) void rmsnorm_bwd_kernel(
                 o[k] = dres ? o[k] + v : v;
                 pw = fmaf(gv[k] * xv[k], r[k], pw);      // 0 past the row end: loads read 0
             }
-            if constexpr (FULL) store_run<TO, TOK, true>(dx + off + fb * L + lane, 0, L, o);
+            if (FULL && !live) pw = 0.0f;
+            if constexpr (FULL) { if (live) store_run<TO, TOK, true>(dx + off + fb * L + lane, 0, L, o); }
             else store_run<TO, TOK>(dx + off + f * L, l0, L, o);
             // over the groups of the slice (consecutive lanes), in a fixed order
 #pragma unroll
@@ -232,16 +255,17 @@ __global__ __launch_bounds__(THREADS) void rmsnorm_bwd_kernel(
             float xv[TOK], gv[TOK];
             unpack_run(xr[i], xv);
             unpack_run(gr[i], gv);
-            if (sl + i * SL < dim) grad(xv, gv, i * SL);
+            const int64_t fb = own + i * step;
+            if (sl + fb < dim) grad(xv, gv, fb);
         }
-        for (int64_t f = sl + C * SL; f < dim; f += SL) {
+        for (int64_t f = sl + own + C * step; f < dim; f += step) {
             float xv[TOK], gv[TOK];
             load_run<T, TOK, FULL>(xb + f * L, l0, L, xv);
             load_run<T, TOK, FULL>(gb + f * L, l0, L, gv);
             grad(xv, gv, f - sl);
         }
     };
-    if (l0 - grp * TOK + Smem::kTile <= L) body(std::true_type{});
+    if (whole) body(std::true_type{});
     else body(std::false_type{});
 }
 
@@ -278,47 +302,64 @@ __global__ __launch_bounds__(kFinFeat * kFinRows) void rmsnorm_bwd_finalize(cons
     }
 }
 
-// 8 groups where tiles of 8 give two blocks for each CU, else 4.
-template <typename T>
-bool wide_tiles(const RmsArgs& a) {
-    constexpr int64_t kTile = 8 * Storage<T>::kPerVec;
-    return a.batch * ((a.seqlen + kTile - 1) / kTile) >= 512;
-}
-
-template <typename T, typename TO, int GROUPS, int THREADS>
-void fwd_g(const RmsArgs& a, hipStream_t s) {
+template <typename T, typename TO, int GROUPS, int THREADS, int KEPT>
+hipError_t fwd_g(const RmsArgs& a, hipStream_t s) {
     constexpr int64_t kTile = GROUPS * Storage<T>::kPerVec;
-    hipLaunchKernelGGL((rmsnorm_fwd_kernel<T, TO, GROUPS, THREADS>),
+    hipLaunchKernelGGL((rmsnorm_fwd_kernel<T, TO, GROUPS, THREADS, KEPT>),
                        dim3((unsigned)((a.seqlen + kTile - 1) / kTile), (unsigned)a.batch), dim3(THREADS), 0, s,
                        static_cast<const T*>(a.x), a.w, a.eps, static_cast<TO*>(a.out), a.rstd_out, a.dim, a.seqlen);
+    return hipGetLastError();
 }
+
+// 8 groups where tiles of 8 give each CU a block, else 4 (us, 8 and 4 groups, bf16: 256 tiles
+// of 8, 4 x 4096 x 768: 8.1, 11.5; 8 x 2048 x 2048: 26.7, 30.1; 128 tiles, 8 x 1024 x 2048:
+// 14.8, 13.7; 32 tiles, 1 x 2048 x 4096: 19.8, 12.6).  1024 threads, with few features 256:
+// of 1024 most slices would be empty (16 x 8192 x 128 bf16: 9.5 against 33; 1 x 4096 x 32:
+// 3.1 against 5.6).  Rows that end inside a 64-byte piece of a line share their lines between
+// tiles, which go to different XCDs: tiles of 64 tokens from half as many on (8 x 1000 x 2048:
+// bf16 32.6 against 37 with 4 groups, fp32 42 against 51 with 8; 64 x 1000 x 2048 fp32: 318
+// against 392).
+constexpr int64_t kSmallDim = 256;
 
 template <typename T, typename TO>
 hipError_t fwd_t(const RmsArgs& a, hipStream_t s) {
-    if (wide_tiles<T>(a)) fwd_g<T, TO, 8, 1024>(a, s);
-    else fwd_g<T, TO, 4, 1024>(a, s);
-    return hipGetLastError();
+    constexpr int64_t kTile = 8 * Storage<T>::kPerVec;
+    const bool wide = a.batch * ((a.seqlen + kTile - 1) / kTile) >= kCus;
+    const bool split_lines = a.seqlen * (int64_t)sizeof(T) % 64 != 0;
+    if (split_lines && a.dim > kSmallDim && a.batch * ((a.seqlen + 63) / 64) >= kCus / 2)
+        return fwd_g<T, TO, 64 / Storage<T>::kPerVec, 1024, 8>(a, s);
+    if (a.dim <= kSmallDim) return wide ? fwd_g<T, TO, 8, 256, 4>(a, s) : fwd_g<T, TO, 4, 256, 4>(a, s);
+    return wide ? fwd_g<T, TO, 8, 1024, 8>(a, s) : fwd_g<T, TO, 4, 1024, 8>(a, s);
 }
 
-// returns the tiles per row
-template <typename T, typename TO, int GROUPS, int THREADS>
-int64_t bwd_g(const RmsArgs& a, hipStream_t s) {
-    constexpr int64_t kTile = GROUPS * Storage<T>::kPerVec;
-    static_assert(kTile >= kRmsTile, "the workspace holds a partial per kRmsTile tokens");
-    const int64_t row_tiles = (a.seqlen + kTile - 1) / kTile;
-    hipLaunchKernelGGL((rmsnorm_bwd_kernel<T, TO, GROUPS, THREADS>), dim3((unsigned)row_tiles, (unsigned)a.batch),
+template <typename T, typename TO, int THREADS, int KEPT>
+hipError_t bwd_g(const RmsArgs& a, hipStream_t s) {
+    constexpr int64_t kSlices = THREADS * (int64_t)Storage<T>::kPerVec / kRmsTile;
+    const int64_t row_tiles = (a.seqlen + kRmsTile - 1) / kRmsTile;
+    // Blocks that share a tile: as many as leave no CU two, each with features of its own (us,
+    // 1, 2, 4, 8 blocks, bf16, 32 tiles, 1 x 2048 x 4096: 57, 40, 31, 27; 64 tiles, 8 x 512 x
+    // 2048: 32, 24, 21, 27; 128 tiles, 4 x 2048 x 768: 16.6, 14.8, 19.9; 256 tiles, 8 x 2048 x
+    // 2048: 58, 61; fp32, 128 tiles, 8 x 1024 x 2048: 63, 61, 65).
+    unsigned parts = 1;
+    while (parts < 8 && a.batch * row_tiles * parts * 2 <= kCus && a.dim > kSlices * parts) parts *= 2;
+    hipLaunchKernelGGL((rmsnorm_bwd_kernel<T, TO, THREADS, KEPT>), dim3((unsigned)row_tiles, (unsigned)a.batch, parts),
                        dim3(THREADS), 0, s, static_cast<const T*>(a.x), a.w, a.rstd, static_cast<const T*>(a.dout),
                        static_cast<const T*>(a.dres), static_cast<TO*>(a.out), a.partial, a.dim, a.seqlen);
-    return row_tiles;
-}
-
-template <typename T, typename TO>
-hipError_t bwd_t(const RmsArgs& a, hipStream_t s) {
-    const int64_t rows = a.batch * (wide_tiles<T>(a) ? bwd_g<T, TO, 8, 512>(a, s) : bwd_g<T, TO, 4, 1024>(a, s));
     if (hipError_t e = hipGetLastError()) return e;
     hipLaunchKernelGGL(rmsnorm_bwd_finalize, dim3((unsigned)((a.dim + kFinFeat - 1) / kFinFeat)),
-                       dim3(kFinFeat * kFinRows), 0, s, a.partial, a.dw, rows, a.dim);
+                       dim3(kFinFeat * kFinRows), 0, s, a.partial, a.dw, a.batch * row_tiles, a.dim);
     return hipGetLastError();
+}
+
+// 1024 threads, 512 where that leaves a thread at most two features (16 x 8192 x 128: 31 us
+// against 42 in bf16, 45 against 51 in fp32; 4 x 4096 x 768 bf16: 27.5 against 22.5).  At 1024
+// threads a bf16 lane holds 4 features (8 spill 67 VGPRs: 160 us against 129 at 8 x 4096 x
+// 2048), an fp32 lane, with half the tokens, 8 (257 against 281 there with 4).
+template <typename T, typename TO>
+hipError_t bwd_t(const RmsArgs& a, hipStream_t s) {
+    constexpr int64_t kSlices = 1024 * (int64_t)Storage<T>::kPerVec / kRmsTile;
+    if (a.dim <= 2 * kSlices) return bwd_g<T, TO, 512, 4>(a, s);
+    return bwd_g<T, TO, 1024, Storage<T>::kPerVec == 8 ? 4 : 8>(a, s);
 }
 
 }  // namespace

@@ -220,6 +220,15 @@ def test_load_follows_lib_path(tmp_path):
     assert L.load()._name == old
 
 
+def test_norm_workspace_keeps_its_size():
+    """The RMSNorm backward's workspace is a partial row per 64 tokens and 16 rows, in whole 256
+    bytes: what callers that sized their buffers by it have."""
+    lib = _lib()
+    for b, d, L in [(1, 1, 1), (8, 2048, 4096), (4, 768, 2048), (2, 2560, 3001), (64, 2048, 1), (3, 7, 65)]:
+        want = 4 * (b * ((L + 63) // 64) + 16) * d
+        assert lib.packmamba_rmsnorm_bwd_workspace_size(b, d, L) == (want + 255) // 256 * 256, (b, d, L)
+
+
 def test_stream_without_the_raw_getter(monkeypatch):
     """A torch build that lacks the raw stream getter gives the stream through its public API."""
     from types import SimpleNamespace

@@ -1,6 +1,7 @@
-"""GPU parity of RMSNorm around its launch rules: narrow and wide tiles (below and from 512 tiles
-of 8 vectors), features kept in registers and beyond them, tiles that cross the row end, and
-partial rows around the finalize's 32 row groups."""
+"""GPU parity of RMSNorm around its launch rules: the forward's narrow and wide tiles (below and
+from 256 tiles of 8 vectors) and its few-features form, the backward's one to eight blocks a tile,
+features kept in registers and beyond them, tiles that cross the row end, partial rows around the
+finalize's 32 row groups, and a workspace of exactly the reported size."""
 import numpy as np
 import pytest
 
@@ -8,10 +9,13 @@ from gpu_common import TOL, act, assert_close, f32, host, note
 
 pytestmark = pytest.mark.gpu
 
-# narrow: 4 vectors a row, 256 slices, 8 kept: 2048 features; wide: 8 vectors, 128 or 64
-# slices: 1024 and 512 kept features
-SHAPES = [(1, 2047, 33), (1, 2049, 31), (2, 300, 1023), (3, 7, 16 * 33 + 1),
-          (8, 511, 4096), (8, 513, 4089), (16, 1025, 2041), (512, 17, 9)]
+# forward: 2048 features kept in narrow tiles, 1024 in wide ones (256 threads, up to 256
+# features: 256, 128).  Backward: 512 kept by one block, 1024 by two, ... 4096 by eight
+SHAPES = [(1, 2047, 33), (1, 2049, 31), (1, 2049, 65), (2, 300, 1023), (3, 7, 16 * 33 + 1),
+          (8, 511, 4096), (8, 513, 4089), (16, 1025, 2041), (512, 17, 9),
+          (4, 256, 4096), (4, 257, 4101), (300, 130, 65), (2, 255, 70), (1, 129, 64),
+          (1, 4097, 128), (2, 4095, 190), (1, 2049, 64 * 40), (1, 1025, 64 * 70 - 1), (2, 1024, 64 * 64),
+          (1, 800, 64 * 129), (8, 300, 1000), (2, 520, 72)]
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -26,7 +30,10 @@ def test_rmsnorm_tiles(shape, dtype):
     note(f"rmsnorm tiles {shape} {dtype}")
     out32 = dtype == "bf16"
     o, rs = P.rmsnorm_fwd(x, w, out_f32=out32)
-    dx, dw = P.rmsnorm_bwd(x, w, rs, g, dresidual=res, out_f32=out32)
+    need = P.load().packmamba_rmsnorm_bwd_workspace_size(*shape)
+    buf = torch.full((need + 4096,), 0x5a, dtype=torch.uint8, device="cuda")
+    dx, dw = P.rmsnorm_bwd(x, w, rs, g, dresidual=res, out_f32=out32, workspace=buf[:need])
+    assert bool((buf[need:] == 0x5a).all())
     x, g, res, w = x.double(), g.double(), res.double(), w.double()[None, :, None]
     r = torch.rsqrt((x * x).mean(1, keepdim=True) + 1e-5)
     dot = (g * w * x).sum(1, keepdim=True)
