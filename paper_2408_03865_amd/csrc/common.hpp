@@ -89,6 +89,8 @@ template <typename T, int K>
 struct RawRun {
     static constexpr bool kHalf = K * sizeof(T) == 8;
     static constexpr int kVecs = kHalf ? 1 : K / Storage<T>::kPerVec;
+    static constexpr int kPer = K / kVecs;               // elements of a vector
+    using Vec = std::conditional_t<kHalf, typename Storage<T>::Half, typename Storage<T>::Vec>;
     static_assert(kHalf || K % Storage<T>::kPerVec == 0, "whole vectors");
     std::conditional_t<kHalf, u32x2, u32x4> w[kVecs];
 };
@@ -98,8 +100,7 @@ __device__ __forceinline__ RawRun<T, K> load_raw(const T* __restrict__ row, int6
     R r;
 #pragma unroll
     for (int i = 0; i < R::kVecs; ++i) {
-        using V = std::conditional_t<R::kHalf, typename Storage<T>::Half, typename Storage<T>::Vec>;
-        const V* p = reinterpret_cast<const V*>(row + l0 + i * Storage<T>::kPerVec);
+        const auto* p = reinterpret_cast<const typename R::Vec*>(row + l0 + i * R::kPer);
         if constexpr (NT) r.w[i] = __builtin_nontemporal_load(p);
         else r.w[i] = *p;
     }
@@ -121,6 +122,42 @@ __device__ __forceinline__ void unpack_run(const RawRun<T, K>& r, float* v) {
     } else {
 #pragma unroll
         for (int i = 0; i < RawRun<T, K>::kVecs; ++i) Storage<T>::unpack(r.w[i], v + i * Storage<T>::kPerVec);
+    }
+}
+
+// The same for a run that may cross or lie beyond the row end: load_part loads the vectors
+// that lie inside the row, unpack_part reads the one that crosses its end, if any, element by
+// element; the elements beyond the end are 0.  The loads of several runs are all on their way
+// before the first wait, where branches with a load on either side (load_run) wait one after
+// the other.
+template <typename T, int K, bool FULL>
+__device__ __forceinline__ RawRun<T, K> load_part(const T* __restrict__ row, int64_t l0, int64_t L) {
+    if constexpr (FULL) {
+        return load_raw<T, K>(row, l0);
+    } else {
+        using R = RawRun<T, K>;
+        R r{};
+#pragma unroll
+        for (int i = 0; i < R::kVecs; ++i)
+            if (l0 + (i + 1) * R::kPer <= L) r.w[i] = *reinterpret_cast<const typename R::Vec*>(row + l0 + i * R::kPer);
+        return r;
+    }
+}
+template <typename T, int K, bool FULL>
+__device__ __forceinline__ void unpack_part(const RawRun<T, K>& r, const T* __restrict__ row, int64_t l0, int64_t L,
+                                            float* v) {
+    unpack_run(r, v);
+    if constexpr (!FULL) {
+        constexpr int PV = RawRun<T, K>::kPer;
+        if (L % PV == 0) return;
+#pragma unroll
+        for (int i = 0; i < K / PV; ++i) {
+            const int64_t l = l0 + i * PV;
+            if (l < L && l + PV > L) {
+#pragma unroll
+                for (int q = 0; q < PV; ++q) v[i * PV + q] = l + q < L ? Storage<T>::load1(row + l + q) : 0.0f;
+            }
+        }
     }
 }
 

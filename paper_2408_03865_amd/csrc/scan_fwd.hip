@@ -42,11 +42,13 @@ constexpr int kCH = 256;                // tokens per chunk
 template <int LANES>
 struct __attribute__((aligned(16))) FwdSmem {
     // [state][four of the lane's tokens][lane][token]: consecutive lanes read consecutive
-    // 16-byte words
+    // 16-byte words.  The padding puts the words that 8 neighbouring threads stage, those of
+    // the same lanes among them, into different banks (4 x 2048 x 1536 fp32: 110 -> 108 us).
     static constexpr int K = kCH / LANES, kRows = kThreads / LANES;
-    float B[kN][K / 4][LANES][4];
-    float C[kN][K / 4][LANES][4];
-    float M[K / 4][LANES][4];   // 0, or -inf on a sequence start
+    static constexpr int kStride4 = LANES + (LANES == 16 ? 2 : LANES == 32 ? 4 : 0);
+    float B[kN][K / 4][kStride4][4];
+    float C[kN][K / 4][kStride4][4];
+    float M[K / 4][kStride4][4];   // 0, or -inf on a sequence start
     float A2[kRows][kN];        // A * log2(e)
     float carry[kRows][kN];     // state after the previous chunk
     float pseg[kRows][kN];      // aggregate pass: product of the multipliers so far
@@ -99,7 +101,7 @@ __device__ __forceinline__ float chain_maps(const float2* __restrict__ maps, int
 
 // AGG: aggregate pass over one segment (no C, no outputs), writes its map (P, H).
 template <typename T, typename TO, int LANES, bool AGG>
-__global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
+__global__ __launch_bounds__(kThreads, LANES == 16 ? 3 : 1) void scan_fwd_kernel(FwdParams p) {
     constexpr int PV = Storage<T>::kPerVec;
     using Smem = FwdSmem<LANES>;
     constexpr int K = Smem::K, kRows = Smem::kRows, CH = kCH;
@@ -145,8 +147,9 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
     const float dbias = p.delta_bias ? p.delta_bias[d] : 0.0f;
 
     const int64_t nchunk = (L + CH - 1) / CH;
-    // The inputs of one full chunk that this thread loads, as stored: its own tokens of u,
-    // delta and z, its part of the block's B and C, and a position index.
+    // The inputs of one chunk that this thread loads, as stored: its own tokens of u, delta and
+    // z, its part of the block's B and C, and a position index.  A chunk that crosses the row
+    // end is loaded so too where there are registers for it (!AHEAD).
     constexpr int NB = kN * CH / (kThreads * PV);
     constexpr bool EARLY = AHEAD || NB == 2;      // B and C too before anything is staged
     struct Inputs {
@@ -154,18 +157,19 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
         RawRun<T, PV> b[NB], c[NB];
         int pos;
     } in;
-    const auto load_inputs = [&](int64_t c) {
+    const auto load_inputs = [&](auto full_tag, int64_t c) {
+        constexpr bool FULL = decltype(full_tag)::value;
         const int64_t lb = c * CH, l0 = lb + (int64_t)j * K;
-        in.u = load_raw<T, K>(ur, l0);
-        in.d = load_raw<T, K>(dr, l0);
-        if (AHEAD && !AGG && zr) in.z = load_raw<T, K>(zr, l0);
+        in.u = load_part<T, K, FULL>(ur, l0, L);
+        in.d = load_part<T, K, FULL>(dr, l0, L);
+        if (AHEAD && !AGG && zr) in.z = load_part<T, K, FULL>(zr, l0, L);
 #pragma unroll
         for (int i = 0; i < (EARLY ? NB : 0); ++i) {
             const int idx = (i * kThreads + tid) * PV, n = idx / CH, t = idx - n * CH;
-            in.b[i] = load_raw<T, PV>(Bb + (int64_t)n * L, lb + t);
-            if (!AGG) in.c[i] = load_raw<T, PV>(Cb + (int64_t)n * L, lb + t);
+            in.b[i] = load_part<T, PV, FULL>(Bb + (int64_t)n * L, lb + t, L);
+            if (!AGG) in.c[i] = load_part<T, PV, FULL>(Cb + (int64_t)n * L, lb + t, L);
         }
-        in.pos = pr[lb + tid];
+        in.pos = FULL || lb + tid < L ? pr[lb + tid] : 1;
     };
     // One chunk; FULL (block-uniform) means the chunk lies inside the row, so every load
     // and store is unconditional.  `next`: the chunk to load ahead of the state loop, or -1.
@@ -173,22 +177,27 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
         constexpr bool FULL = decltype(full_tag)::value;
         const int64_t lb = c * CH;
         const int64_t l0 = lb + (int64_t)j * K;
-        // this lane's inputs, loaded first in a full chunk so that their latency
-        // overlaps the staging below
-        if constexpr (FULL && !AHEAD) load_inputs(c);
+        constexpr bool RAW = FULL || !AHEAD;      // the inputs are in `in`
+        // this lane's inputs, loaded first so that their latency overlaps the staging below
+        if constexpr (!AHEAD) load_inputs(full_tag, c);
         // ---- stage B, C and the reset mask of this chunk in LDS ----
         static_assert(kThreads == CH, "a thread stages one position index");
 #pragma unroll(EARLY ? NB : 1)
         for (int i = 0; i < NB; ++i) {
             const int idx = (i * kThreads + tid) * PV, n = idx / CH, t = idx - n * CH;
             float vb[PV], vc[PV];
-            if constexpr (FULL && EARLY) {
-                unpack_run(in.b[i], vb);
-                if (!AGG) unpack_run(in.c[i], vc);
+            const T* const br = Bb + (int64_t)n * L;
+            const T* const cr = Cb + (int64_t)n * L;
+            RawRun<T, PV> rb, rc;
+            if constexpr (RAW && EARLY) {
+                rb = in.b[i];
+                rc = in.c[i];
             } else {
-                load_run<T, PV, FULL>(Bb + (int64_t)n * L, lb + t, L, vb);
-                if (!AGG) load_run<T, PV, FULL>(Cb + (int64_t)n * L, lb + t, L, vc);
+                rb = load_part<T, PV, FULL>(br, lb + t, L);
+                if (!AGG) rc = load_part<T, PV, FULL>(cr, lb + t, L);
             }
+            unpack_part<T, PV, FULL>(rb, br, lb + t, L, vb);
+            if (!AGG) unpack_part<T, PV, FULL>(rc, cr, lb + t, L, vc);
 #pragma unroll
             for (int q = 0; q < PV; q += 4) {
                 const int h = (t + q) % K / 4, l = (t + q) / K;
@@ -196,23 +205,21 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
                 if (!AGG) *reinterpret_cast<f32x4*>(sm.C[n][h][l]) = f32x4{vc[q], vc[q + 1], vc[q + 2], vc[q + 3]};
             }
         }
-        {
-            const int64_t l = lb + tid;
-            const int ps = FULL ? in.pos : l < L ? pr[l] : 1;
-            sm.M[tid % K / 4][tid / K][tid % 4] = ps == 0 ? -INFINITY : 0.0f;
-        }
+        const int ps = RAW ? in.pos : lb + tid < L ? pr[lb + tid] : 1;
+        sm.M[tid % K / 4][tid / K][tid % 4] = ps == 0 ? -INFINITY : 0.0f;
         __syncthreads();
 
         // ---- per-token inputs of this lane ----
         float dt[K], du[K], y[K], M[K];
         {
             float uv[K];
-            if constexpr (FULL) {
-                unpack_run(in.u, uv);
-                unpack_run(in.d, dt);
+            if constexpr (RAW) {
+                unpack_part<T, K, FULL>(in.u, ur, l0, L, uv);
+                unpack_part<T, K, FULL>(in.d, dr, l0, L, dt);
             } else {
-                load_run<T, K, FULL>(ur, l0, L, uv);
-                load_run<T, K, FULL>(dr, l0, L, dt);
+                const RawRun<T, K> ru = load_part<T, K, FULL>(ur, l0, L), rd = load_part<T, K, FULL>(dr, l0, L);
+                unpack_part<T, K, FULL>(ru, ur, l0, L, uv);
+                unpack_part<T, K, FULL>(rd, dr, l0, L, dt);
             }
 #pragma unroll
             for (int k = 0; k < K; ++k) {
@@ -231,7 +238,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
         }
         // the next chunk's inputs, on their way while this one's states are worked through
         const RawRun<T, K> wz = in.z;
-        if (AHEAD && next >= 0) load_inputs(next);
+        if (AHEAD && next >= 0) load_inputs(std::true_type{}, next);
         // product of the lane's multipliers as one exp2 (0 if the lane holds a start)
         float S = 0.0f, Mf = 0.0f;
 #pragma unroll
@@ -246,10 +253,15 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
             const float A2n = sm.A2[r][n];
             const float cin = sm.carry[r][n];
             float a[K], bx[K];
+            f32x4 bv[K / 4];
+#pragma unroll
+            for (int k = 0; k < K / 4; ++k) bv[k] = *reinterpret_cast<const f32x4*>(sm.B[n][k][j]);
+            // all four reads first: left to itself, the scheduler issues the last two after the
+            // first two have been used (8 x 200 x 4096, fp32 54 -> 49 us, bf16 54 -> 41)
+            if (LANES == 16) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int k = 0; k < K; k += 4) {
-                const f32x4 bv = *reinterpret_cast<const f32x4*>(sm.B[n][k / 4][j]);
-                const float bb[4] = {bv.x, bv.y, bv.z, bv.w};
+                const float bb[4] = {bv[k / 4].x, bv[k / 4].y, bv[k / 4].z, bv[k / 4].w};
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     a[k + q] = fast_exp2(fmaf(dt[k + q], A2n, M[k + q]));
@@ -299,7 +311,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
             if (zr) {
                 float zv[K], g[K];
                 if constexpr (FULL && AHEAD) unpack_run(wz, zv);
-                else load_run<T, K, FULL>(zr, l0, L, zv);
+                else unpack_part<T, K, FULL>(load_part<T, K, FULL>(zr, l0, L), zr, l0, L, zv);
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     const float sz = sigmoid_f(zv[k]);
@@ -326,14 +338,14 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(FwdParams p) {
         // the product of the multipliers is exactly 0 for every channel and state of the
         // block (a sequence start, or underflow of a long decay), the earlier chunks
         // contribute exactly nothing, and the walk stops.
-        if (AHEAD) load_inputs(c1 - 1);            // (a segment that is aggregated lies inside the row)
+        if (AHEAD) load_inputs(std::true_type{}, c1 - 1);   // (a segment that is aggregated lies inside the row)
         for (int64_t c = c1 - 1; c >= c0; --c) {
             chunk(std::true_type{}, c, c > c0 ? c - 1 : -1);
             if (!__syncthreads_or(tid < kRows * kN && sm.pseg[0][tid] != 0.0f)) break;
         }
     } else {
         const int64_t full = L / CH;              // chunks that lie inside the row
-        if (AHEAD && c0 < full) load_inputs(c0);
+        if (AHEAD && c0 < full) load_inputs(std::true_type{}, c0);
         for (int64_t c = c0; c < c1; ++c) {
             if (c < full) chunk(std::true_type{}, c, c + 1 < min(c1, full) ? c + 1 : -1);
             else chunk(std::false_type{}, c, -1);
