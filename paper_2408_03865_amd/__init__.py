@@ -169,11 +169,14 @@ def rmsnorm_bwd(x, weight, rstd, dout, dresidual=None, workspace=None, out_f32: 
 def segments(batch: int, dim: int, seqlen: int, direction: str = "bwd") -> int:
     """Segments per row the scan forward ("fwd") or backward ("bwd") uses for this shape
     (1: rows are not split).  Mirrors the rule of the library's launchers, for tests and
-    reports only."""
+    reports only; the bf16 forward leaves rows of up to 2048 tokens whole above 256 blocks of 16
+    channels."""
     target = {"fwd": 768, "bwd": 1536}[direction]
     blocks = batch * ((dim + 15) // 16)
     units = (seqlen + 255) // 256
-    if blocks * 2 >= target or units < 2 or (direction == "fwd" and blocks >= 256 and seqlen <= 4096):
+    if blocks * 2 >= target or units < 2:
+        return 1
+    if direction == "fwd" and blocks > 192 and seqlen <= 1536:
         return 1
     nseg = min((target + blocks - 1) // blocks, units)
     per = (units + nseg - 1) // nseg

@@ -197,7 +197,8 @@ size_t packmamba_selective_scan_fwd_saved_states_size(int64_t batch, int64_t dim
 size_t packmamba_selective_scan_fwd_workspace_size(int64_t batch, int64_t dim, int64_t seqlen,
                                                    int32_t dstate) {
     if (check_shape(batch, dim, seqlen) || dstate != kN) return 0;
-    return seg_ws(batch, dim, pm::scan_fwd_plan(batch, dim, seqlen).seg);
+    // fp32 splits whatever bf16 does
+    return seg_ws(batch, dim, pm::scan_fwd_plan(batch, dim, seqlen, true).seg);
 }
 
 int packmamba_selective_scan_fwd(const void* u, const void* delta, const float* A, const void* B,
@@ -218,7 +219,7 @@ int packmamba_selective_scan_fwd(const void* u, const void* delta, const float* 
         !aligned16(position_indices) || !aligned16(out) || !aligned16(saved_states) ||
         !aligned16(workspace) || !aligned16(initial_state) || !aligned16(final_state))
         return PACKMAMBA_ERR_ALIGN;
-    const size_t need = seg_ws(batch, dim, pm::scan_fwd_plan(batch, dim, seqlen).seg);
+    const size_t need = seg_ws(batch, dim, pm::scan_fwd_plan(batch, dim, seqlen, dtype == PACKMAMBA_F32).seg);
     if (need && (!workspace || workspace_bytes < need)) return PACKMAMBA_ERR_WORKSPACE;
     pm::ScanArgs a{};
     if (need) set_seg_ws(a, workspace, batch, dim);

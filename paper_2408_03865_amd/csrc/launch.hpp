@@ -163,25 +163,33 @@ inline SegPlan scan_segments(int64_t batch, int64_t dim, int64_t seqlen, int64_t
 }
 
 // The forward's split and its lanes per channel (scan forward kernel; 16 lanes: blocks of 16
-// channels, 32: of 8, 64: of 4).  Times in us, bf16, saving states:
-//  - from 448 blocks of 16 channels: 16 lanes, unsplit (512 blocks, 4 x 8192 x 2048: 396
-//    against 444 with 32 lanes; 640: 261 both);
-//  - from 256 blocks, rows of up to 4096 tokens (from 384 blocks any): 32 lanes, unsplit, no
-//    aggregate pass (4 x 2048 x 1536: 89 against 105; 4 x 1024 x 1024: 50 against 63 in four
-//    segments).  Longer rows in 256 blocks are split: 2 x 8192 x 2048 takes 190 (short
-//    sequences, which an aggregate pass skips quickly) to 268 (long ones) split and 246 unsplit;
-//  - below that, rows split; where even single-unit segments leave less than one round of
-//    768 blocks of 16, 32 lanes (1 x 1000 x 512: 32 against 37), and 64 below 192 (1 x 256 x
-//    64: 19 against 22; 1 x 700 x 128: 32 against 38).
+// channels, 32: of 8, 64: of 4; `blocks` counts blocks of 16).  What decides is how many rounds
+// the blocks take, three blocks a CU (two of the fp32 kernel of 32 lanes, 188 VGPRs), and how
+// much of its segment the aggregate pass walks: all of it without a sequence start, one chunk
+// with short sequences.  Us, saving states, split in 16 lanes with short sequences to with one
+// sequence a row, against unsplit in 16 and 32 lanes:
+//   bf16  384 blocks, 4 x 2048 x 1536: unsplit 92, 78; 400, 5 x 2048 x 1280: 93, 108
+//         352, 1 x 2048 x 5632: 81 to 106 against 91, 77; 1 x 4096 x 5632: 140 to 200, 177, 149
+//         256, 1 x 1536 x 4096: 46 to 54 against 56, 46; 1 x 2048 x 4096: 53 to 70, 74, 61
+//         208, 1 x 1024 x 3328: 38 to 38 against 37, 31; 1 x 2048 x 3328: 59 to 71, 73, 59
+//   fp32  384, 4 x 2048 x 1536: 106, 110; 400: 106, 125
+//         352, 1 x 1536 x 5632: 78 to 90 against 78, 83; 1 x 2048 x 5632: 96 to 120, 102, 108
+//         256, 1 x 1536 x 4096: 55 to 64 against 68, 53; 1 x 2048 x 4096: 63 to 79, 91, 69
+// So rows are whole from 384 blocks on, and from 193 where they are short enough for that to
+// cost no length law much: up to 1536 tokens, above 256 blocks in bf16 up to 2048.  Unsplit, 32
+// lanes where they take one round, 16 above.
+// Split rows: where even single-unit segments leave less than one round of 768 blocks of 16, 32
+// lanes (1 x 1000 x 512: 32 against 37), and 64 below 192 (1 x 256 x 64: 19 against 22; 1 x 700
+// x 128: 32 against 38).
 struct FwdPlan {
     SegPlan seg;
     int lanes;
 };
-inline FwdPlan scan_fwd_plan(int64_t batch, int64_t dim, int64_t seqlen) {
+inline FwdPlan scan_fwd_plan(int64_t batch, int64_t dim, int64_t seqlen, bool f32) {
     const int64_t blocks = batch * ((dim + 15) / 16);
     const int64_t units = (seqlen + kSegUnit - 1) / kSegUnit;
-    if (blocks >= 448) return {{1, units * kSegUnit}, 16};
-    if (blocks >= 256 && (seqlen <= 4096 || blocks >= 384)) return {{1, units * kSegUnit}, 32};
+    if (blocks >= 384 || (blocks > 192 && seqlen <= 1536) || (!f32 && blocks > 256 && seqlen <= 2048))
+        return {{1, units * kSegUnit}, blocks <= (f32 ? 256 : 384) ? 32 : 16};
     return {scan_segments(batch, dim, seqlen, kSegTargetFwd), blocks * units < 192 ? 64 : blocks * units < 768 ? 32 : 16};
 }
 

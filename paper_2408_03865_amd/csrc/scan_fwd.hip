@@ -477,7 +477,7 @@ hipError_t launch_t(const ScanArgs& a, hipStream_t s) {
                            dim3((unsigned)((a.dim + kShortCh - 1) / kShortCh), (unsigned)a.batch), dim3(kThreads), 0, s, p);
         return hipGetLastError();
     }
-    const FwdPlan plan = scan_fwd_plan(a.batch, a.dim, a.seqlen);
+    const FwdPlan plan = scan_fwd_plan(a.batch, a.dim, a.seqlen, std::is_same_v<T, float>);
     const SegPlan sp = plan.seg;
     static_assert(kSegUnit % kCH == 0, "segments hold whole chunks");
     p.seg_chunks = sp.seg_len / kCH;
