@@ -372,9 +372,8 @@ __global__ __launch_bounds__(kThreads, LANES == 16 ? 3 : 1) void scan_fwd_kernel
 // token the pass is its states: each is read and written once, 16 bytes a lane, a wave
 // 1 KB in a row.  B, C and the reset mask of the whole row are in LDS.
 // 64 x 4096 channels, bf16, one token: 313 -> 9.0 us (4.0 TB/s), the chunk kernel's work
-// being a whole 256-token chunk.  The walk is serial in the tokens, so the limit lies where
-// few rows meet the chunk kernel's time: at 32 tokens 27 against 25 us for 1536 channels
-// and 120 against 327 us for 64 x 4096.
+// being a whole 256-token chunk.  The walk is serial in the tokens: the rows it takes are in
+// short_row().
 constexpr int64_t kShortRow = 32;
 constexpr int kShortCh = kThreads / 4;       // channels per block
 
@@ -461,6 +460,20 @@ hipError_t launch_lanes(const ScanArgs& a, FwdParams p, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Longest rows of the short kernel, where its time meets the chunk kernel's (us, chunk kernel
+// second; both are latencies where blocks are few, 16 channels each): 4 blocks, 20 tokens 8.6,
+// 9.3, 24 tokens 10.1, 8.5; 192 blocks, 24 tokens 10.4, 10.2, 28 tokens 12.0, 11.4; 384 blocks,
+// 32 tokens 13.5, 13.4; 2048 blocks, 32 tokens 15, 43.  Its 4-byte loads of fp32 run through a
+// line a tensor and channel, 32 tokens, that very many rows evict from the caches: 64 x 4096
+// channels, 28 tokens 248, 311, 32 tokens 331, 312.
+template <typename T>
+int64_t short_row(const ScanArgs& a) {
+    const int64_t blocks = a.batch * ((a.dim + 15) / 16);
+    if (blocks < 128) return 20;
+    if (blocks < 384) return 24;
+    return std::is_same_v<T, float> && blocks >= 8192 ? 28 : kShortRow;
+}
+
 template <typename T, typename TO>
 hipError_t launch_t(const ScanArgs& a, hipStream_t s) {
     static_assert(kCH == kDzfChunk, "the dz factor layout follows the forward's chunk");
@@ -472,7 +485,7 @@ hipError_t launch_t(const ScanArgs& a, hipStream_t s) {
     p.dim = a.dim; p.L = a.seqlen;
     p.nchunk_states = (int)((a.seqlen + kStride - 1) / kStride);
     p.softplus = a.softplus;
-    if (a.seqlen <= kShortRow && !a.states) {
+    if (a.seqlen <= short_row<T>(a) && !a.states) {
         hipLaunchKernelGGL((scan_fwd_short_kernel<T, TO>),
                            dim3((unsigned)((a.dim + kShortCh - 1) / kShortCh), (unsigned)a.batch), dim3(kThreads), 0, s, p);
         return hipGetLastError();

@@ -1,11 +1,12 @@
 """GPU parity of the paths whose launch depends on the row length: the scan forward's short-row
-kernel (no saved states, up to 32 tokens) on both sides of its limit, and the conv forward's
+kernel (no saved states, up to 20 to 32 tokens by the number of channels) on both sides of its
+limits, and the conv forward's
 lanes per row, tiles per row and rows per lane, against the oracle."""
 import numpy as np
 import pytest
 
 import workloads as W
-from gpu_common import TOL, act, assert_close, f32, host, i32, note
+from gpu_common import TOL, act, assert_close, bf16_bits_of, f32, host, i32, note, rne_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -15,8 +16,8 @@ def _cfg(batch, dim, seqlen, width, dtype):
                     8800 + batch * 13 + dim * 3 + seqlen)
 
 
-# tokens: one vector and less, the limit of the short kernel and one token on either side;
-# channels: one, a block of 64 and one on either side
+# tokens: one vector and less, and around the most that the short kernel ever takes; channels:
+# one, a block of 64 and one on either side
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("states", [False, True], ids=["fresh", "continued"])
 @pytest.mark.parametrize("shape", [(1, 1, 1), (3, 65, 1), (2, 64, 2), (2, 63, 7), (1, 130, 31), (2, 40, 32), (2, 40, 33)],
@@ -46,6 +47,37 @@ def test_scan_forward_short_rows(shape, states, dtype):
                                pos=pos, h0=h0, return_final=True)
         assert_close("out", host(got), ref, TOL["f32"])        # same inputs and fp32 arithmetic for both types
         assert_close("final", host(fin), rfin, TOL["f32"])
+
+
+# the short kernel's limits and one token beyond: 20 tokens below 128 blocks of 16 channels, 24
+# below 384, 32 from there, in fp32 28 from 8192 blocks.  The bf16 output is the fp32 one, rounded
+# once.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(2, 40, 3), (2, 40, 20), (2, 40, 21), (16, 127, 24), (16, 127, 25), (48, 120, 32),
+                                   (48, 120, 33), (127, 1030, 28), (127, 1030, 29)], ids=lambda s: "x".join(map(str, s)))
+def test_scan_forward_short_row_limits(shape, dtype):
+    import oracle as O
+    import paper_2408_03865_amd as P
+    batch, dim, L = shape
+    d = W.make_inputs(_cfg(batch, dim, L, 4, dtype), variant="general")
+    h0 = np.random.default_rng(L).standard_normal((batch, dim, 16)).astype(np.float32)
+    pos = d["pos"].copy()
+    pos[::2] = np.arange(L) + 5                              # every other row continues a sequence throughout
+    note(f"short scan limits {shape} {dtype}")
+    for softplus in (True, False):
+        delta = d["delta"] if softplus else np.abs(d["delta"])
+        g = {k: act(d[k], dtype) for k in ("u", "B", "C", "z")}
+        a = (g["u"], act(delta, dtype), f32(d["A"]), g["B"], g["C"], f32(d["D"]), g["z"], f32(d["delta_bias"]) if softplus else None,
+             softplus, i32(pos))
+        got, fin = P.selective_scan_fwd(*a, out_f32=dtype == "bf16", initial_state=f32(h0), return_final=True)
+        ref, rfin = O.scan_fwd(u=d["u"], delta=delta, A=d["A"], B=d["B"], C=d["C"], D=d["D"], z=d["z"],
+                               delta_bias=d["delta_bias"] if softplus else None, delta_softplus=softplus, pos=pos, h0=h0,
+                               return_final=True)
+        assert_close("out", host(got), ref, TOL["f32"])        # same inputs and fp32 arithmetic for both types
+        assert_close("final", host(fin), rfin, TOL["f32"])
+        if dtype == "bf16":
+            b16, fin16 = P.selective_scan_fwd(*a, initial_state=f32(h0), return_final=True)
+            assert np.array_equal(bf16_bits_of(b16), rne_bf16(got)) and np.array_equal(host(fin16), host(fin))
 
 
 # tokens around one lane's vector (4 and 8), around the powers of two of lanes per row, a wave's
