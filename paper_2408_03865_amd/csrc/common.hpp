@@ -30,7 +30,6 @@ typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
 typedef u32x2 u32x2_a4 __attribute__((aligned(4)));
 typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
 typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
-typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
@@ -90,20 +89,31 @@ struct RawRun {
     static constexpr bool kHalf = K * sizeof(T) == 8;
     static constexpr int kVecs = kHalf ? 1 : K / Storage<T>::kPerVec;
     static constexpr int kPer = K / kVecs;               // elements of a vector
-    using Vec = std::conditional_t<kHalf, typename Storage<T>::Half, typename Storage<T>::Vec>;
     static_assert(kHalf || K % Storage<T>::kPerVec == 0, "whole vectors");
     std::conditional_t<kHalf, u32x2, u32x4> w[kVecs];
 };
+// One of its vectors.  The types that carry the element's alignment are named here and are no
+// template argument, which would lose it: the compiler may then take the address for a
+// vector-aligned one, and where it is the same for the whole wave load it through the scalar
+// cache, which drops the address's low bits.
+template <typename T, int K, bool NT = false>
+__device__ __forceinline__ auto load_vec(const T* __restrict__ p) {
+    if constexpr (RawRun<T, K>::kHalf) {
+        const auto* v = reinterpret_cast<const typename Storage<T>::Half*>(p);
+        if constexpr (NT) return u32x2(__builtin_nontemporal_load(v));
+        else return u32x2(*v);
+    } else {
+        const auto* v = reinterpret_cast<const typename Storage<T>::Vec*>(p);
+        if constexpr (NT) return u32x4(__builtin_nontemporal_load(v));
+        else return u32x4(*v);
+    }
+}
 template <typename T, int K, bool NT = false>
 __device__ __forceinline__ RawRun<T, K> load_raw(const T* __restrict__ row, int64_t l0) {
     using R = RawRun<T, K>;
     R r;
 #pragma unroll
-    for (int i = 0; i < R::kVecs; ++i) {
-        const auto* p = reinterpret_cast<const typename R::Vec*>(row + l0 + i * R::kPer);
-        if constexpr (NT) r.w[i] = __builtin_nontemporal_load(p);
-        else r.w[i] = *p;
-    }
+    for (int i = 0; i < R::kVecs; ++i) r.w[i] = load_vec<T, K, NT>(row + l0 + i * R::kPer);
     return r;
 }
 // The same, non-temporal: for inputs read once, so that they do not take cache space
@@ -139,7 +149,7 @@ __device__ __forceinline__ RawRun<T, K> load_part(const T* __restrict__ row, int
         R r{};
 #pragma unroll
         for (int i = 0; i < R::kVecs; ++i)
-            if (l0 + (i + 1) * R::kPer <= L) r.w[i] = *reinterpret_cast<const typename R::Vec*>(row + l0 + i * R::kPer);
+            if (l0 + (i + 1) * R::kPer <= L) r.w[i] = load_vec<T, K>(row + l0 + i * R::kPer);
         return r;
     }
 }
