@@ -5,7 +5,8 @@
 // the forward keeps the tap reaching k tokens back iff k <= pos[l]; the
 // backward's dx takes the next width-1 tokens' indices ("reverse indices") and
 // keeps tap k iff pos[j+k] >= k.
-//  - Forward: one wave per (tile of tokens, channels), described at its kernel.
+//  - Forward: one wave per (tile of tokens, channels) or a block per row, described at their
+//    kernels.
 //  - Backward: one wave per (row, segment), described at its kernel.
 #include "common.hpp"
 #include "launch.hpp"
@@ -13,7 +14,7 @@
 namespace pm {
 namespace {
 
-constexpr int kTok = 8;        // the halo vector of the backward
+constexpr int kTok = 8;        // the halo vector of the backward and of the forward by rows
 constexpr int kTokBwd = 8;     // tokens per thread per step (backward)
 constexpr int kThreads = 256;
 // Waves of one channel that the backward gathers in one block, and the elements up to which
@@ -61,6 +62,20 @@ __device__ __forceinline__ void load_row_halo(const T* __restrict__ xinit, int64
     }
 }
 
+// The row's last W-1 inputs, copied as stored (reaching into xinit for short rows).
+template <typename T, typename TO, int W>
+__device__ __forceinline__ void store_xfinal(const T* __restrict__ x, const ConvStates<T, TO>& st, int64_t row, int64_t L) {
+    constexpr int H = W - 1;
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+        const int64_t m = L - H + i;
+        T v{};
+        if (m >= 0) v = x[row * L + m];
+        else if (st.xinit) v = st.xinit[row * H + H + m];
+        st.xfinal[row * H + i] = v;
+    }
+}
+
 // Forward: one wave per (tile of tokens, R channels).  Each lane owns KT consecutive
 // tokens (one 16-byte vector of x), a row takes 2^lanes_log2 lanes of a wave, and a wave
 // holds 64 >> lanes_log2 rows at once, so that rows shorter than a wave's span (one token
@@ -69,9 +84,9 @@ __device__ __forceinline__ void load_row_halo(const T* __restrict__ xinit, int64
 // position indices are read and their tap masks compared once for the R, and R vectors
 // per lane are in flight.  The W-1 tokens before a lane's come from the lane before it by
 // a lane shift, only lane 0 of a later tile reads them from memory: a pass reads x once
-// and writes out once.  Bound by HBM at long rows (8 x 4096 x 4096: fp32 191 us, 5.6 TB/s,
-// against 233 us with a block per row and the halo read again; bf16 105 against 99);
-// one token of 64 x 4096 channels takes 5.3 us against 177 us with a block per row.
+// and writes out once.  Bound by HBM at long rows (8 x 4096 x 4096 fp32: 182 us, 5.9 TB/s,
+// against 223 us with 8 tokens a lane); one token of 64 x 4096 channels takes 4 us against 153
+// with a block per row.
 template <typename T, typename TO, int W, int R>
 __global__ __launch_bounds__(kThreads) void conv1d_fwd_kernel(
     const T* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias,
@@ -154,17 +169,7 @@ __global__ __launch_bounds__(kThreads) void conv1d_fwd_kernel(
         if (d >= dim) return;
         TO* orow = out + row * L;
         if (l0 < L) store_run<TO, KT>(orow, l0, L, o);
-        // the row's last W-1 inputs, copied as stored (reaching into xinit for short rows)
-        if (st.xfinal && first && tile == 0) {
-#pragma unroll
-            for (int i = 0; i < H; ++i) {
-                const int64_t m = L - H + i;
-                T v{};
-                if (m >= 0) v = x[row * L + m];
-                else if (st.xinit) v = st.xinit[row * H + H + m];
-                st.xfinal[row * H + i] = v;
-            }
-        }
+        if (st.xfinal && first && tile == 0) store_xfinal<T, TO, W>(x, st, row, L);
     };
     if (all_live) {
 #pragma unroll
@@ -173,6 +178,49 @@ __global__ __launch_bounds__(kThreads) void conv1d_fwd_kernel(
 #pragma unroll
         for (int r = 0; r < R; ++r) channel(std::false_type{}, r);
     }
+}
+
+// Forward of bf16 rows of a few thousand tokens, aligned to vectors (conv_fwd_by_row): a block
+// per row, which it walks 2048 tokens at a time, each lane reading its vector and the one before
+// it, which the lane or block before it has brought into the cache.
+template <typename T, typename TO, int W>
+__global__ __launch_bounds__(kThreads) void conv1d_fwd_row_kernel(
+    const T* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias,
+    const int32_t* __restrict__ pos, TO* __restrict__ out, ConvStates<T, TO> st, int64_t dim,
+    int64_t L, int silu) {
+    constexpr int KT = Storage<T>::kPerVec;
+    static_assert(KT == kTok, "the halo is the vector before");
+    const int64_t row = blockIdx.x;
+    const int64_t b = row / dim, d = row - b * dim;
+    const T* xr = x + row * L;
+    TO* orow = out + row * L;
+    const int32_t* pr = pos + b * L;
+    float wk[W];
+#pragma unroll
+    for (int k = 0; k < W; ++k) wk[k] = w[d * W + k];
+    const float b0 = bias ? bias[d] : 0.0f;
+
+    for (int64_t l0 = (int64_t)threadIdx.x * KT; l0 < L; l0 += (int64_t)kThreads * KT) {
+        const RawRun<T, KT> rx = load_raw<T, KT>(xr, l0);
+        RawRun<T, KT> rh{};
+        if (l0 > 0) rh = load_raw<T, KT>(xr, l0 - KT);
+        int p[KT];
+        load_pos<KT, true>(pr, l0, L, p);
+        float xs[2 * KT], o[KT];
+        if (l0 > 0) unpack_run(rh, xs);
+        else load_row_halo<T, W>(st.xinit, row, xs);
+        unpack_run(rx, xs + KT);
+#pragma unroll
+        for (int t = 0; t < KT; ++t) {
+            float v = fmaf(wk[W - 1], xs[KT + t], b0);               // tap 0: position indices are >= 0
+#pragma unroll
+            for (int k = 1; k < W; ++k)
+                if (k <= p[t]) v = fmaf(wk[W - 1 - k], xs[KT + t - k], v);
+            o[t] = silu ? v * sigmoid_f(v) : v;
+        }
+        store_run<TO, KT, true>(orow, l0, L, o);
+    }
+    if (st.xfinal && threadIdx.x == 0) store_xfinal<T, TO, W>(x, st, row, L);
 }
 
 // Backward: one wave per (row, segment), walking the segment from its end in steps
@@ -378,8 +426,19 @@ __global__ void conv1d_bwd_finalize(const float* __restrict__ partial, float* __
     else if (dbias) dbias[d] = s;
 }
 
+// bf16 rows that a block each walks.  Us, one wave per tile against a block per row:
+// 2 x 6208 x 5120 52, 43; 1 x 7872 x 5120 34, 27; 2 x 16192 x 2048 53, 43; 1 x 21704 x 1536 29,
+// 24; 4 x 3072 x 2048 22, 19; 8 x 4096 x 4096 103, 95.  Beyond the limits, the second measured
+// with row ends looked for: 12 x 1088 x 5120 62, 68 (a block's 2048 tokens are half empty);
+// 1 x 32768 x 5120 141, 190 and 2 x 65536 x 1024 95, 123; 1 x 16384 x 256 5.1, 7.3 (too few
+// rows); unaligned rows, 8 x 4095 x 4096 119, 121, 2 x 12289 x 2048 43, 46.  In fp32 a lane's 8
+// tokens are two vectors, 32 bytes apart from the next lane's: 182, 223 at 8 x 4096 x 4096.
+bool conv_fwd_by_row(const ConvArgs& a) {
+    return a.seqlen % kTok == 0 && a.seqlen > 2048 && a.seqlen < 32768 && a.batch * a.dim >= 1024;
+}
+
 // Rows per lane of the forward: 2 when that leaves 8 waves for each of the 1024 SIMDs (1, 2, 4
-// and 8 rows at 8 x 4096 x 4096: 113, 105, 105, 131 us in bf16, 229, 191, 206, 249 in fp32).
+// and 8 rows at 8 x 4096 x 4096 fp32: 229, 191, 206, 249 us).
 constexpr int kFwdRows = 2;
 constexpr int64_t kFwdWaves = 8192;
 
@@ -398,6 +457,13 @@ hipError_t conv_fwd_w(const ConvArgs& a, hipStream_t s) {
     const dim3 grid((unsigned)((waves + kThreads / 64 - 1) / (kThreads / 64)), (unsigned)a.batch);
     const T* x = static_cast<const T*>(a.x);
     TO* o = static_cast<TO*>(a.out);
+    if constexpr (Storage<T>::kPerVec == kTok) {
+        if (conv_fwd_by_row(a)) {
+            hipLaunchKernelGGL((conv1d_fwd_row_kernel<T, TO, W>), dim3((unsigned)(a.batch * a.dim)), dim3(kThreads), 0, s,
+                               x, a.w, a.bias, a.pos, o, st, a.dim, a.seqlen, a.silu);
+            return hipGetLastError();
+        }
+    }
     if (many)
         hipLaunchKernelGGL((conv1d_fwd_kernel<T, TO, W, kFwdRows>), grid, dim3(kThreads), 0, s, x, a.w, a.bias, a.pos,
                            o, st, a.dim, a.seqlen, a.silu, lanes_log2, (int)ntiles, waves);

@@ -91,11 +91,24 @@ CONV_SHAPES = [(1, 1, 1), (2, 70, 2), (3, 33, 5), (2, 5, 8), (2, 17, 9), (1, 9, 
 @pytest.mark.parametrize("width", [2, 3, 4])
 @pytest.mark.parametrize("shape", CONV_SHAPES, ids=lambda s: "x".join(map(str, s)))
 def test_conv_forward_lanes_and_tiles(shape, width, dtype):
+    if shape[0] * shape[1] * shape[2] > 1 << 20 and width != 4:
+        pytest.skip("the large shapes run at one width")
+    _conv_forward(shape, width, dtype)
+
+
+# bf16 rows that a block each walks (aligned, 2049 to 32767 tokens, 1024 rows), and each limit
+# missed: one row fewer, 2048 tokens, unaligned
+@pytest.mark.parametrize("shape", [(1, 1024, 2056), (4, 257, 4104), (1, 1023, 2056), (2, 520, 2048), (1, 1024, 2060)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("width", [2, 3, 4])
+def test_conv_forward_by_row(shape, width):
+    _conv_forward(shape, width, "bf16")
+
+
+def _conv_forward(shape, width, dtype):
     import oracle as O
     import paper_2408_03865_amd as P
     batch, dim, L = shape
-    if batch * dim * L > 1 << 20 and width != 4:
-        pytest.skip("the large shapes run at one width")
     rng = np.random.default_rng(batch + dim + L + width)
     rnd = W.bf16_round if dtype == "bf16" else (lambda a: a)
     x = rnd(rng.standard_normal((batch, dim, L)).astype(np.float32))
