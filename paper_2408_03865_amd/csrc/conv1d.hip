@@ -17,12 +17,7 @@ namespace {
 constexpr int kTok = 8;        // the halo vector of the backward and of the forward by rows
 constexpr int kTokBwd = 8;     // tokens per thread per step (backward)
 constexpr int kThreads = 256;
-// Waves of one channel that the backward gathers in one block, and the elements up to which
-// it does: the block sums the parameter gradients and saves the finalize's launch (3 us of
-// 37 at 4 x 2048 x 1536, 2.5 of 58 at 2 x 8192 x 2048), but its waves read batch rows far apart
-// at the same time, which costs the large shapes more (187 -> 250 us at 8 x 4096 x 4096).
-constexpr int64_t kConvBwdGather = (int64_t)1 << 25;
-constexpr int kConvBwdParts = 16;
+constexpr int kConvBwdParts = 16;     // most waves of one channel that the backward gathers in a block
 
 // N position indices from l0 (N a multiple of 4); beyond L they read 0.  FULL: the
 // caller guarantees l0 + N <= L
@@ -493,6 +488,26 @@ hipError_t conv_fwd_t(const ConvArgs& a, hipStream_t s) {
     }
 }
 
+// Whether a block takes all `parts` waves (batch rows x segments) of a channel.  It sums the
+// parameter gradients and saves the finalize's launch, 2.5 us; but it needs that many free places
+// on one CU at once, which costs where blocks queue, the more so where they load its four SIMDs
+// unevenly, and its waves read batch rows far apart.  Us, a wave per block against gathered, bf16
+// rows of 500 tokens (fp32 and 64 tokens lie within a few percent):
+//   4 waves x 3072 channels 19.9, 17.9; x 5120 28, 27;  5 x 1024 11.5, 10.9; x 1536 14.6, 15.3
+//   6 x 1024 13.3, 12.2; x 1536 16.2, 17.5;  8 x 1024 15.7, 12.7; x 2048 26, 25; x 5120 51, 57
+//   9 x 512 12.2, 11.4; x 1024 16.7, 21.4;  12 x 512 14.6, 12; x 1024 21.8, 23.1
+//   16 x 512 17.4, 13.2; x 1024 28, 27; x 2048 45, 52;  9 x 704 x 5120: 61, 111
+// Longer waves: 6 of them, 1 x 4096 x 700 10.8, 8.3; 1 x 8192 x 700 15.5, 15.6; 2 x 3648 x 768 15.7,
+// 18; 14, 1 x 16384 x 300 14.9, 17.8; 16, 16 x 2048 x 256 18.6, 13.3; 8, 8 x 4096 x 512 27, 24.
+// Most elements: 2 x 8192 x 2048 45.3, 41.7, fp32 92, 89; 2^26 of them, 4 x 8192 x 2048 77, 79, fp32 177,
+// 182; 8 x 4096 x 4096 157, 188.
+bool conv_bwd_gathers(const ConvArgs& a, int64_t parts) {
+    if (parts > kConvBwdParts || a.batch * a.dim * a.seqlen > (int64_t)1 << 25) return false;
+    if (parts <= 4) return true;
+    if (parts % 4 == 0) return parts * a.dim <= 8192;
+    return parts * a.dim <= 6144 && a.batch * a.dim * a.seqlen <= (int64_t)1 << 22;
+}
+
 template <typename T, typename TO, int W, bool DXF>
 hipError_t conv_bwd_w(const ConvArgs& a, hipStream_t s) {
     const ConvStates<T, TO> st{static_cast<const T*>(a.xinit), nullptr, static_cast<const T*>(a.dxfinal),
@@ -501,7 +516,7 @@ hipError_t conv_bwd_w(const ConvArgs& a, hipStream_t s) {
     const T* g = static_cast<const T*>(a.dout);
     TO* dx = static_cast<TO*>(a.out);
     const int64_t nseg = conv_bwd_segments(a.batch, a.dim, a.seqlen), parts = a.batch * nseg;
-    if (parts <= kConvBwdParts && a.batch * a.dim * a.seqlen <= kConvBwdGather) {
+    if (conv_bwd_gathers(a, parts)) {
         hipLaunchKernelGGL((conv1d_bwd_kernel<T, TO, W, kTokBwd, DXF, true>), dim3((unsigned)a.dim),
                            dim3((unsigned)(64 * parts)), 0, s, x, a.w, a.bias, a.pos, g, dx, a.partial, a.dw, a.dbias,
                            st, a.dim, a.seqlen, (int)nseg, a.silu);

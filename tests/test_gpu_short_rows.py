@@ -129,23 +129,39 @@ def _conv_forward(shape, width, dtype):
     assert_close("plain", host(plain), O.conv1d_fwd(x, w, None, pos, silu=False), TOL["f32"])
 
 
-# waves per channel that one block gathers: 1, 3, 16 (4 rows of 4 segments), and one wave per
-# block beyond 16 (17 batch rows) or beyond the size limit (the last shape)
+# (batch, channels, tokens): waves per channel.  One block gathers up to 4, or up to 16 within
+# 8192 waves in all where they are a multiple of 4, else within 6144 and 2^22 elements: both sides
+# of each limit
+GATHERED = {(1, 3, 70): 1, (3, 5, 1030): 9, (4, 6, 2048): 16, (4, 6, 2049): 20, (17, 4, 30): 17, (4, 1100, 70): 4,
+            (6, 1024, 100): 6, (6, 1025, 100): 6, (6, 700, 990): 6, (6, 700, 1000): 6, (8, 1024, 70): 8, (8, 1025, 70): 8,
+            (1, 600, 3500): 7, (4, 4100, 2050): 4}
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("shape", [(1, 3, 70), (3, 5, 1030), (4, 6, 2049), (17, 4, 30), (4, 4100, 2050)],
-                         ids=lambda s: "x".join(map(str, s)))
-def test_conv_backward_gathered_waves(shape, dtype):
+@pytest.mark.parametrize("states", [False, True], ids=["fresh", "continued"])
+@pytest.mark.parametrize("shape", GATHERED, ids=lambda s: "x".join(map(str, s)))
+def test_conv_backward_gathered_waves(shape, states, dtype):
     import oracle as O
     import paper_2408_03865_amd as P
     batch, dim, L = shape
+    if states and batch * dim * L > 1 << 22:
+        pytest.skip("the large shapes run without states")
+    need = P.load().packmamba_causal_conv1d_bwd_workspace_size(batch, dim, L, 4)
+    assert need == -(-GATHERED[shape] * dim * 5 * 4 // 256) * 256      # a partial per wave, channel and sum
     rng = np.random.default_rng(batch * 7 + dim + L)
     rnd = W.bf16_round if dtype == "bf16" else (lambda a: a)
     x, g = (rnd(rng.standard_normal((batch, dim, L)).astype(np.float32)) for _ in range(2))
+    xi, dxf = (rnd(rng.standard_normal((batch, dim, 3)).astype(np.float32)) for _ in range(2))
     w = rng.uniform(-0.5, 0.5, (dim, 4)).astype(np.float32)
     bias = rng.uniform(-0.5, 0.5, dim).astype(np.float32)
     pos = W.positions_from_lengths(W.draw_row_lengths(("lognormal", 4.0, 1.0, 1, L), rng, batch, L), L)
-    note(f"conv bwd {shape} {dtype}")
-    dx, dw, db = P.causal_conv1d_bwd(act(x, dtype), f32(w), f32(bias), i32(pos), act(g, dtype), out_f32=dtype == "bf16")
-    ref = O.conv1d_bwd(x, w, bias, pos, g)
-    for k, got in (("dx", dx), ("dw", dw), ("dbias", db)):
-        assert_close(k, host(got), ref[k], TOL["f32"])
+    if states:                                             # every row continues a sequence
+        first = np.argmax(np.concatenate([pos[:, 1:] == 0, np.ones((batch, 1), bool)], 1), 1) + 1
+        for b in range(batch):
+            pos[b, :first[b]] += 1 + b % 4
+    note(f"conv bwd {shape} {dtype} states={states}")
+    kw = dict(initial_x=act(xi, dtype), dfinal_x=act(dxf, dtype)) if states else {}
+    got = P.causal_conv1d_bwd(act(x, dtype), f32(w), f32(bias), i32(pos), act(g, dtype), out_f32=dtype == "bf16", **kw)
+    ref = O.conv1d_bwd(x, w, bias, pos, g, **(dict(xinit=xi, dxfinal=dxf) if states else {}))
+    for k, v in zip(("dx", "dw", "dbias", "dxinit"), got):
+        assert_close(k, host(v), ref[k], TOL["f32"])
