@@ -78,32 +78,31 @@ __device__ __forceinline__ void store_xfinal(const T* __restrict__ x, const Conv
 // Forward: one wave per (tile of tokens, R channels).  Each lane owns KT consecutive
 // tokens (one 16-byte vector of x), a row takes 2^lanes_log2 lanes of a wave, and a wave
 // holds 64 >> lanes_log2 rows at once, so that rows shorter than a wave's span (one token
-// in a decode step) fill it too; rows longer than a wave's span are cut into tiles, one
-// wave each.  The wave walks R such sets of rows of one batch row, all loads first: the
+// in a decode step) fill it too; rows longer than a wave's span (LONG) are cut into tiles,
+// one wave each, which then has a channel's weights in scalar registers.  The wave walks R such sets of rows of one batch row, all loads first: the
 // position indices are read and their tap masks compared once for the R, and R vectors
 // per lane are in flight.  The W-1 tokens before a lane's come from the lane before it by
 // a lane shift, only lane 0 of a later tile reads them from memory: a pass reads x once
 // and writes out once.  Bound by HBM at long rows (8 x 4096 x 4096 fp32: 182 us, 5.9 TB/s,
 // against 223 us with 8 tokens a lane); one token of 64 x 4096 channels takes 4 us against 153
 // with a block per row.
-template <typename T, typename TO, int W, int R>
+template <typename T, typename TO, int W, int R, bool LONG>
 __global__ __launch_bounds__(kThreads) void conv1d_fwd_kernel(
     const T* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias,
     const int32_t* __restrict__ pos, TO* __restrict__ out, ConvStates<T, TO> st, int64_t dim,
-    int64_t L, int silu, int lanes_log2, int ntiles, int64_t waves) {
+    int64_t L, int silu, int lanes_log2, uint32_t ntiles, uint32_t waves) {
     constexpr int KT = Storage<T>::kPerVec;
     constexpr int H = W - 1;
     const int lane = (int)(threadIdx.x & 63);
-    const int64_t wave = (int64_t)blockIdx.x * (kThreads / 64) +
-                         __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t wave = blockIdx.x * (kThreads / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (wave >= waves) return;
     const int64_t b = blockIdx.y;
-    const int64_t group = wave / ntiles;
-    const int tile = (int)(wave - group * ntiles);
-    const int rows = 64 >> lanes_log2;                  // rows a wave holds at once
-    const int vec = lane & ((1 << lanes_log2) - 1);
-    const int64_t l0 = ((int64_t)tile * 64 + vec) * KT;  // more than one tile only with 64 lanes a row
-    const int64_t d0 = group * (R * rows) + (lane >> lanes_log2);
+    const uint32_t group = LONG ? wave / ntiles : wave;
+    const int tile = LONG ? (int)(wave - group * ntiles) : 0;
+    const int rows = LONG ? 1 : 64 >> lanes_log2;       // rows a wave holds at once
+    const int vec = LONG ? lane : lane & ((1 << lanes_log2) - 1);
+    const int64_t l0 = ((int64_t)tile * 64 + vec) * KT;
+    const int64_t d0 = (int64_t)group * (R * rows) + (LONG ? 0 : lane >> lanes_log2);
     const int32_t* pr = pos + b * L;
     const bool first = vec == 0;
 
@@ -121,8 +120,10 @@ __global__ __launch_bounds__(kThreads) void conv1d_fwd_kernel(
         for (int t = 0; t < H; ++t) halo[r][t] = 0.0f;
         if (first) {
             if (tile > 0) {
+                float v[4];
+                unpack_run(load_raw<T, 4>(xr, l0 - 4), v);
 #pragma unroll
-                for (int t = 0; t < H; ++t) halo[r][t] = Storage<T>::load1(xr + l0 - H + t);
+                for (int t = 0; t < H; ++t) halo[r][t] = v[4 - H + t];
             } else if (st.xinit) {
 #pragma unroll
                 for (int t = 0; t < H; ++t) halo[r][t] = Storage<T>::load1(st.xinit + row * H + t);
@@ -134,13 +135,19 @@ __global__ __launch_bounds__(kThreads) void conv1d_fwd_kernel(
     }
     int p[KT];
     load_pos<KT>(pr, l0, L, p);
+    const bool full = LONG && ((int64_t)tile + 1) * 64 * KT <= L;
     int pmin = W - 1;                                   // lowest index of the lane's tokens inside the row
+    if (full) {
 #pragma unroll
-    for (int t = 0; t < KT; ++t) pmin = l0 + t < L ? min(pmin, p[t]) : pmin;
+        for (int t = 0; t < KT; ++t) pmin = min(pmin, p[t]);
+    } else {
+#pragma unroll
+        for (int t = 0; t < KT; ++t) pmin = l0 + t < L ? min(pmin, p[t]) : pmin;
+    }
     const bool all_live = __all(pmin >= W - 1);          // no tap of the wave is cut off
 
-    auto channel = [&](auto live_tag, const int r) {
-        constexpr bool LIVE = decltype(live_tag)::value;
+    auto channel = [&](auto live_tag, auto silu_tag, const int r) {
+        constexpr bool LIVE = decltype(live_tag)::value, SILU = decltype(silu_tag)::value;
         const int64_t d = d0 + r * rows;
         const int64_t row = b * dim + (d < dim ? d : dim - 1);
         float xs[H + KT];
@@ -154,6 +161,12 @@ __global__ __launch_bounds__(kThreads) void conv1d_fwd_kernel(
             const float prev = dpp<kWaveShr1>(0.0f, xs[KT + t]);     // the same token of the lane before
             xs[t] = first ? halo[r][t] : prev;
         }
+        if (KT == 8) {
+            // 24 masks are compared again for each channel: kept for the next, they spill from
+            // the scalar registers, at two instructions a mask
+#pragma unroll
+            for (int t = 0; t < KT; ++t) asm volatile("" : "+v"(p[t]));
+        }
         float o[KT];
 #pragma unroll
         for (int t = 0; t < KT; ++t) {
@@ -163,19 +176,24 @@ __global__ __launch_bounds__(kThreads) void conv1d_fwd_kernel(
                 const float u = fmaf(wk[r][W - 1 - k], xs[H + t - k], v);
                 v = (LIVE || k <= p[t]) ? u : v;
             }
-            o[t] = silu ? v * sigmoid_f(v) : v;
+            o[t] = SILU ? v * sigmoid_f(v) : v;
         }
         if (d >= dim) return;
         TO* orow = out + row * L;
-        if (l0 < L) store_run<TO, KT>(orow, l0, L, o);
+        if (full) store_run<TO, KT, true>(orow, l0, L, o);
+        else if (l0 < L) store_run<TO, KT>(orow, l0, L, o);
         if (st.xfinal && first && tile == 0) store_xfinal<T, TO, W>(x, st, row, L);
     };
-    if (all_live) {
+    const auto channels = [&](auto live_tag, auto silu_tag) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) channel(std::true_type{}, r);
+        for (int r = 0; r < R; ++r) channel(live_tag, silu_tag, r);
+    };
+    if (silu) {
+        if (all_live) channels(std::true_type{}, std::true_type{});
+        else channels(std::false_type{}, std::true_type{});
     } else {
-#pragma unroll
-        for (int r = 0; r < R; ++r) channel(std::false_type{}, r);
+        if (all_live) channels(std::true_type{}, std::false_type{});
+        else channels(std::false_type{}, std::false_type{});
     }
 }
 
@@ -443,40 +461,50 @@ bool conv_fwd_by_row(const ConvArgs& a) {
     return a.seqlen % kTok == 0 && a.seqlen > 2048 && a.seqlen < 32768 && a.batch * a.dim >= 1024;
 }
 
-// Rows per lane of the forward: 2 when that leaves 8 waves for each of the 1024 SIMDs (1, 2, 4
-// and 8 rows at 8 x 4096 x 4096 fp32: 229, 191, 206, 249 us).
+// Rows per lane of the tiled forward where that leaves 8 waves for each of the 1024 SIMDs, else 1.
+// Rows of several tiles: 16 tokens a lane (2 and 4 rows, us: fp32 15 x 1152 x 768 19.3, 18.3;
+// 4 x 2304 x 1024 13.6, 12.4; 4 x 2048 x 1536 17.7, 16.6; 8 x 4096 x 4096 175, 179; bf16 15 x 1152 x
+// 768 13.8, 14.7; 4 x 2048 x 1536 9.9, 10.7; 12 x 1088 x 5120 54, 52).  Shorter rows: 2 (fp32
+// 16 x 250 x 2048 12.5, 13.1; 64 x 100 x 1024 9.6, 10.6).
+template <typename T>
+constexpr int kFwdRowsLong = 16 / Storage<T>::kPerVec;
 constexpr int kFwdRows = 2;
 constexpr int64_t kFwdWaves = 8192;
+
+template <typename T, typename TO, int W, int R, bool LONG>
+hipError_t conv_fwd_r(const ConvArgs& a, hipStream_t s, int lanes_log2, int64_t ntiles) {
+    const int64_t set = (int64_t)R * (64 >> lanes_log2);           // channels of a wave
+    const int64_t waves = (a.dim + set - 1) / set * ntiles;
+    const ConvStates<T, TO> st{static_cast<const T*>(a.xinit), static_cast<T*>(a.xfinal), nullptr, nullptr};
+    hipLaunchKernelGGL((conv1d_fwd_kernel<T, TO, W, R, LONG>),
+                       dim3((unsigned)((waves + kThreads / 64 - 1) / (kThreads / 64)), (unsigned)a.batch), dim3(kThreads),
+                       0, s, static_cast<const T*>(a.x), a.w, a.bias, a.pos, static_cast<TO*>(a.out), st, a.dim,
+                       a.seqlen, a.silu, lanes_log2, (uint32_t)ntiles, (uint32_t)waves);
+    return hipGetLastError();
+}
 
 template <typename T, typename TO, int W>
 hipError_t conv_fwd_w(const ConvArgs& a, hipStream_t s) {
     constexpr int KT = Storage<T>::kPerVec;
+    if constexpr (KT == kTok) {
+        if (conv_fwd_by_row(a)) {
+            const ConvStates<T, TO> st{static_cast<const T*>(a.xinit), static_cast<T*>(a.xfinal), nullptr, nullptr};
+            hipLaunchKernelGGL((conv1d_fwd_row_kernel<T, TO, W>), dim3((unsigned)(a.batch * a.dim)), dim3(kThreads), 0, s,
+                               static_cast<const T*>(a.x), a.w, a.bias, a.pos, static_cast<TO*>(a.out), st, a.dim,
+                               a.seqlen, a.silu);
+            return hipGetLastError();
+        }
+    }
     const int64_t nvec = (a.seqlen + KT - 1) / KT;
     int lanes_log2 = 0;
     while (lanes_log2 < 6 && ((int64_t)1 << lanes_log2) < nvec) ++lanes_log2;
     const int64_t ntiles = (nvec + 63) / 64;
-    const int rows = 64 >> lanes_log2;
-    const ConvStates<T, TO> st{static_cast<const T*>(a.xinit), static_cast<T*>(a.xfinal), nullptr, nullptr};
-    const auto waves_at = [&](int r) { return (a.dim + r * rows - 1) / (r * rows) * ntiles; };
-    const bool many = waves_at(kFwdRows) * a.batch >= kFwdWaves;
-    const int64_t waves = waves_at(many ? kFwdRows : 1);
-    const dim3 grid((unsigned)((waves + kThreads / 64 - 1) / (kThreads / 64)), (unsigned)a.batch);
-    const T* x = static_cast<const T*>(a.x);
-    TO* o = static_cast<TO*>(a.out);
-    if constexpr (Storage<T>::kPerVec == kTok) {
-        if (conv_fwd_by_row(a)) {
-            hipLaunchKernelGGL((conv1d_fwd_row_kernel<T, TO, W>), dim3((unsigned)(a.batch * a.dim)), dim3(kThreads), 0, s,
-                               x, a.w, a.bias, a.pos, o, st, a.dim, a.seqlen, a.silu);
-            return hipGetLastError();
-        }
-    }
-    if (many)
-        hipLaunchKernelGGL((conv1d_fwd_kernel<T, TO, W, kFwdRows>), grid, dim3(kThreads), 0, s, x, a.w, a.bias, a.pos,
-                           o, st, a.dim, a.seqlen, a.silu, lanes_log2, (int)ntiles, waves);
-    else
-        hipLaunchKernelGGL((conv1d_fwd_kernel<T, TO, W, 1>), grid, dim3(kThreads), 0, s, x, a.w, a.bias, a.pos, o, st,
-                           a.dim, a.seqlen, a.silu, lanes_log2, (int)ntiles, waves);
-    return hipGetLastError();
+    const auto many = [&](int64_t set) { return (a.dim + set - 1) / set * ntiles * a.batch >= kFwdWaves; };
+    if (lanes_log2 == 6)
+        return many(kFwdRowsLong<T>) ? conv_fwd_r<T, TO, W, kFwdRowsLong<T>, true>(a, s, 6, ntiles)
+                                     : conv_fwd_r<T, TO, W, 1, true>(a, s, 6, ntiles);
+    return many(kFwdRows * (64 >> lanes_log2)) ? conv_fwd_r<T, TO, W, kFwdRows, false>(a, s, lanes_log2, 1)
+                                               : conv_fwd_r<T, TO, W, 1, false>(a, s, lanes_log2, 1);
 }
 
 template <typename T, typename TO>
