@@ -154,6 +154,7 @@ __global__ __launch_bounds__(THREADS) void rmsnorm_fwd_kernel(const T* __restric
 // launch.  Where that leaves CUs idle, gridDim.z blocks (a power of two) share a tile: each
 // sums over all features and writes the gradients of its part of them, every gridDim.z-th of
 // a slice's.  The sum's loads are repeated, from the XCD's L2 that the blocks of a tile share.
+// One block a tile where dx takes the place of x or dh, which the others would still read.
 template <typename T, typename TO, int THREADS, int KEPT>
 __global__ __launch_bounds__(THREADS) void rmsnorm_bwd_kernel(
     const T* __restrict__ x, const float* __restrict__ w, const float* __restrict__ rstd,
@@ -341,7 +342,8 @@ hipError_t bwd_g(const RmsArgs& a, hipStream_t s) {
     // 2048: 32, 24, 21, 27; 128 tiles, 4 x 2048 x 768: 16.6, 14.8, 19.9; 256 tiles, 8 x 2048 x
     // 2048: 58, 61; fp32, 128 tiles, 8 x 1024 x 2048: 63, 61, 65).
     unsigned parts = 1;
-    while (parts < 8 && a.batch * row_tiles * parts * 2 <= kCus && a.dim > kSlices * parts) parts *= 2;
+    const bool in_place = a.out == a.x || a.out == a.dout;
+    while (!in_place && parts < 8 && a.batch * row_tiles * parts * 2 <= kCus && a.dim > kSlices * parts) parts *= 2;
     hipLaunchKernelGGL((rmsnorm_bwd_kernel<T, TO, THREADS, KEPT>), dim3((unsigned)row_tiles, (unsigned)a.batch, parts),
                        dim3(THREADS), 0, s, static_cast<const T*>(a.x), a.w, a.rstd, static_cast<const T*>(a.dout),
                        static_cast<const T*>(a.dres), static_cast<TO*>(a.out), a.partial, a.dim, a.seqlen);

@@ -41,3 +41,48 @@ def test_rmsnorm_tiles(shape, dtype):
     assert_close("out", host(o), host(x * r * w), TOL["f32"])
     assert_close("dx", host(dx), host(r * (g * w - x * r * r * dot / d) + res), TOL["f32"])
     assert_close("dw", host(dw), host((g * x * r).sum((0, 2))), TOL["f32"])
+
+
+# one block a tile, and eight, four and two that share one; ragged rows.  dx in the place of x,
+# dout or the residual's gradient, and the forward's output in the place of x
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(3, 130, 70), (1, 4097, 128), (2, 2049, 190), (1, 1025, 64 * 70 - 1), (1, 1024, 64 * 129),
+                                   (64, 640, 4096 // 16)], ids=lambda s: "x".join(map(str, s)))
+def test_rmsnorm_in_place(shape, dtype):
+    import torch
+    from paper_2408_03865_amd import _lib
+    b, d, L = shape
+    lib, code = _lib.load(), {"f32": 0, "bf16": 1}[dtype]
+    rng = np.random.default_rng(b + d + L)
+    x, g, res = (act(rng.standard_normal(shape, dtype=np.float32), dtype) for _ in range(3))
+    w = f32(rng.uniform(0.5, 1.5, d))
+    rs = torch.empty((b, L), device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    ws = torch.empty(lib.packmamba_rmsnorm_bwd_workspace_size(*shape), dtype=torch.uint8, device="cuda")
+    note(f"rmsnorm in place {shape} {dtype}")
+
+    def fwd(xi, out):
+        assert lib.packmamba_rmsnorm_fwd(xi.data_ptr(), w.data_ptr(), 1e-5, out.data_ptr(), rs.data_ptr(), *shape, code, stream) == 0
+        return out
+
+    def bwd(xi, gi, ri, dx):
+        dw = torch.empty_like(w)
+        assert lib.packmamba_rmsnorm_bwd(xi.data_ptr(), w.data_ptr(), rs.data_ptr(), gi.data_ptr(), ri.data_ptr(), dx.data_ptr(),
+                                         dw.data_ptr(), ws.data_ptr(), ws.numel(), *shape, code, stream) == 0
+        return dx, dw
+
+    def same(got, want):
+        # several blocks of a tile take its features in another order than one: fp32 sums within their
+        # rounding, so that a bf16 result is at most one rounding (2^-7 of it) off
+        assert_close("in place", host(got), host(want), TOL["f32"] if dtype == "f32" else 2.0 ** -7)
+
+    out = fwd(x, torch.empty_like(x))
+    xi = x.clone()
+    assert torch.equal(fwd(xi, xi), out)
+    dx, dw = bwd(x, g, res, torch.empty_like(x))
+    for i in range(3):
+        t = [x, g, res]
+        t[i] = t[i].clone()
+        dx2, dw2 = bwd(*t, t[i])
+        same(dx2, dx)
+        same(dw2, dw)
