@@ -178,9 +178,11 @@ inline SegPlan scan_segments(int64_t batch, int64_t dim, int64_t seqlen, int64_t
 // So rows are whole from 384 blocks on, and from 193 where they are short enough for that to
 // cost no length law much: up to 1536 tokens, above 256 blocks in bf16 up to 2048.  Unsplit, 32
 // lanes where they take one round, 16 above.
-// Split rows: where even single-unit segments leave less than one round of 768 blocks of 16, 32
-// lanes (1 x 1000 x 512: 32 against 37), and 64 below 192 (1 x 256 x 64: 19 against 22; 1 x 700
-// x 128: 32 against 38).
+// Split rows, by their single-unit segments of 16 channels (us, nothing saved, 16, 32, 64 lanes):
+// 32 lanes where they take one round, 768 blocks of them in bf16 (384 segments, 3 x 1000 x 512
+// 22.7, 20.8, 24.4; 512, 2 x 1024 x 1024 23.0, 24.7, 26.8; 720, 3 x 1152 x 768 31.7, 34.0, 38.8) and 512
+// in fp32 (256, 2 x 2000 x 256 22.2, 19.3, 24.0; 384 25.6, 27.4, 27.4; 720 35.9, 42.2, 44.9), above 16;
+// 64 below 192 (128, 4 x 500 x 256 bf16 20.4, 19.0, 17.7; fp32 19.0, 17.1, 16.1).
 struct FwdPlan {
     SegPlan seg;
     int lanes;
@@ -190,7 +192,8 @@ inline FwdPlan scan_fwd_plan(int64_t batch, int64_t dim, int64_t seqlen, bool f3
     const int64_t units = (seqlen + kSegUnit - 1) / kSegUnit;
     if (blocks >= 384 || (blocks > 192 && seqlen <= 1536) || (!f32 && blocks > 256 && seqlen <= 2048))
         return {{1, units * kSegUnit}, blocks <= (f32 ? 256 : 384) ? 32 : 16};
-    return {scan_segments(batch, dim, seqlen, kSegTargetFwd), blocks * units < 192 ? 64 : blocks * units < 768 ? 32 : 16};
+    const int64_t segs = blocks * units;
+    return {scan_segments(batch, dim, seqlen, kSegTargetFwd), segs < 192 ? 64 : segs <= (f32 ? 256 : 384) ? 32 : 16};
 }
 
 hipError_t launch_scan_fwd(const ScanArgs& a, hipStream_t s);

@@ -1,7 +1,8 @@
 """GPU parity of the scan forward in each of its launch shapes (16, 32 or 64 lanes per channel,
-the fp32 forward 16 instead of 32 above 256 blocks of 16 channels; rows split or not) at ragged lengths around the 256-token chunk: outputs, final states, the
-chunk states, and, through the backward, the dz factor, whose order in memory is the same for
-every number of lanes."""
+the fp32 forward 16 instead of 32 above 256 blocks or segments of 16 channels; rows split or
+not) at ragged lengths around the 256-token chunk: outputs, final states, the chunk states,
+and, through the backward, the dz factor, whose order in memory is the same for every number
+of lanes."""
 import numpy as np
 import pytest
 
@@ -13,9 +14,10 @@ pytestmark = pytest.mark.gpu
 # (batch, dim, seqlen): segments
 SHAPES = {
     "64 lanes": [(1, 5, 130), (1, 3, 255), (2, 33, 256), (1, 4, 257), (1, 64, 700)],
-    "32 lanes split": [(2, 300, 1300), (1, 500, 1537)],
+    "32 lanes split": [(2, 300, 1300), (1, 500, 1537), (4, 256, 1000)],
     "32 lanes unsplit": [(16, 250, 300), (20, 247, 511), (24, 256, 77), (13, 250, 1536), (24, 256, 1600)],
-    "16 lanes split": [(1, 1600, 2049), (13, 250, 1537), (16, 256, 1700)],
+    "bf16: 32 lanes split, fp32: 16": [(3, 512, 1000), (5, 96, 2300)],
+    "16 lanes split": [(5, 170, 1700), (1, 1600, 2049), (13, 250, 1537), (16, 256, 1700)],
     "16 lanes unsplit": [(28, 256, 270), (30, 241, 513), (25, 254, 1025)],
     "bf16: 32 lanes unsplit, fp32: 16 lanes split": [(17, 250, 2048), (18, 249, 1601)],
 }
