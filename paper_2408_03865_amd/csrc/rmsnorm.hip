@@ -314,23 +314,50 @@ hipError_t fwd_g(const RmsArgs& a, hipStream_t s) {
 
 // 8 groups where tiles of 8 give each CU a block, else 4 (us, 8 and 4 groups, bf16: 256 tiles
 // of 8, 4 x 4096 x 768: 8.1, 11.5; 8 x 2048 x 2048: 26.7, 30.1; 128 tiles, 8 x 1024 x 2048:
-// 14.8, 13.7; 32 tiles, 1 x 2048 x 4096: 19.8, 12.6).  1024 threads, with few features 256:
-// of 1024 most slices would be empty (16 x 8192 x 128 bf16: 9.5 against 33; 1 x 4096 x 32:
-// 3.1 against 5.6).  Rows that end inside a 64-byte piece of a line share their lines between
-// tiles, which go to different XCDs: tiles of 64 tokens from half as many on (8 x 1000 x 2048:
-// bf16 32.6 against 37 with 4 groups, fp32 42 against 51 with 8; 64 x 1000 x 2048 fp32: 318
-// against 392).
-constexpr int64_t kSmallDim = 256;
+// 14.8, 13.7; 32 tiles, 1 x 2048 x 4096: 19.8, 12.6).  1024 threads; fewer where most slices
+// would have few features or none: up to 256 of them 512 threads (16 x 4096 x 256: bf16 10.4
+// against 12.5 with 256, fp32 20.9 against 26) and 256 up to 128 (16 x 8192 x 128 bf16: 10.6
+// against 15.5 with 512 and 33 with 1024) and in narrow tiles (1 x 4096 x 32: 3.1 against 5.6);
+// in bf16 also up to 512 (5 x 2816 x 512: 7.1 against 11.5; 8 x 4096 x 384 7.9, 11.4; 1 x 2048 x
+// 300 4.1, 5.9; fp32 64 x 256 x 512 11.4, 9.9).
+// Rows that end inside a 64-byte piece of a line share their lines between tiles, which go to
+// different XCDs: tiles of 64 tokens from 96 of them on in bf16, in fp32, whose 64 tokens are two
+// lines, from 64 (us, against the other tiles: bf16 96 tiles, 6 x 1000 x 2048 25.0, 27.4; 94,
+// 2 x 3001 x 2560 47.6, 44.6; fp32 84, 21 x 216 x 5120 71.6, 92.4; 64, 4 x 1000 x 2048 28.8, 28.6;
+// up to 256 features 20 x 12712 x 256: bf16 76 against 105, fp32 111 against 162).
+// Eight kept features leave a CU one block of 1024 threads in bf16, four two: four where tiles
+// just over one round leave the second nearly empty (270 tiles, 30 x 576 x 2560: 44.5 against
+// 49.4; x 1024 15.1, 19.2; 320 tiles, 40 x 512 x 2560 50.6, 50.8; 352 52.6, 51.9), in narrow tiles
+// up to 2048 features (264, 33 x 256 x 768 9.1, 11.7; 384, 12 x 1024 x 2048 21.9, 24.7; x 4096 51.5,
+// 47.2), or where the kept four are all (8 x 1024 x 768 6.7, 7.1).
+constexpr int kSmallDim = 256;
 
 template <typename T, typename TO>
 hipError_t fwd_t(const RmsArgs& a, hipStream_t s) {
+    constexpr bool kBf16 = Storage<T>::kPerVec == 8;
     constexpr int64_t kTile = 8 * Storage<T>::kPerVec;
+    constexpr int kG64 = 64 / Storage<T>::kPerVec;               // groups of a tile of 64 tokens
     const bool wide = a.batch * ((a.seqlen + kTile - 1) / kTile) >= kCus;
     const bool split_lines = a.seqlen * (int64_t)sizeof(T) % 64 != 0;
-    if (split_lines && a.dim > kSmallDim && a.batch * ((a.seqlen + 63) / 64) >= kCus / 2)
-        return fwd_g<T, TO, 64 / Storage<T>::kPerVec, 1024, 8>(a, s);
-    if (a.dim <= kSmallDim) return wide ? fwd_g<T, TO, 8, 256, 4>(a, s) : fwd_g<T, TO, 4, 256, 4>(a, s);
-    return wide ? fwd_g<T, TO, 8, 1024, 8>(a, s) : fwd_g<T, TO, 4, 1024, 8>(a, s);
+    const int64_t tiles64 = a.batch * ((a.seqlen + 63) / 64);
+    const bool by64 = split_lines && tiles64 >= (kBf16 ? kCus * 3 / 8 : kCus / 4);
+    if (a.dim <= kSmallDim) {
+        if (!wide) return fwd_g<T, TO, 4, 256, 4>(a, s);
+        if (split_lines) return fwd_g<T, TO, kG64, 512, 8>(a, s);
+        return a.dim <= kSmallDim / 2 ? fwd_g<T, TO, 8, 256, 4>(a, s) : fwd_g<T, TO, 8, 512, 4>(a, s);
+    }
+    if constexpr (kBf16) {
+        if (a.dim <= 2 * kSmallDim && !by64)
+            return wide ? fwd_g<T, TO, 8, 512, 8>(a, s) : fwd_g<T, TO, 4, 512, 4>(a, s);
+        if (a.dim > 2 * kSmallDim && tiles64 > kCus && tiles64 <= kCus * 5 / 4) return fwd_g<T, TO, 8, 1024, 4>(a, s);
+    }
+    if (by64) return fwd_g<T, TO, kG64, 1024, 8>(a, s);
+    if (wide) return fwd_g<T, TO, 8, 1024, 8>(a, s);
+    if constexpr (kBf16) {
+        const int64_t tiles32 = a.batch * ((a.seqlen + 31) / 32);
+        if (a.dim <= 1024 || (a.dim <= 2048 && tiles32 > kCus)) return fwd_g<T, TO, 4, 1024, 4>(a, s);
+    }
+    return fwd_g<T, TO, 4, 1024, 8>(a, s);
 }
 
 template <typename T, typename TO, int THREADS, int KEPT>

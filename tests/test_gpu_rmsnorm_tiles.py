@@ -9,13 +9,16 @@ from gpu_common import TOL, act, assert_close, f32, host, note
 
 pytestmark = pytest.mark.gpu
 
-# forward: 2048 features kept in narrow tiles, 1024 in wide ones (256 threads, up to 256
-# features: 256, 128).  Backward: 512 kept by one block, 1024 by two, ... 4096 by eight
+# forward: 2048 features kept in narrow tiles, 1024 in wide ones (256 threads, up to 128 features
+# or in narrow tiles: 256, 128; 512 threads, up to 512 features: all; 4 kept of each thread's,
+# bf16 just over 256 tiles: 512).  Backward: 512 kept by one block, 1024 by two, ... 4096 by eight
 SHAPES = [(1, 2047, 33), (1, 2049, 31), (1, 2049, 65), (2, 300, 1023), (3, 7, 16 * 33 + 1),
           (8, 511, 4096), (8, 513, 4089), (16, 1025, 2041), (512, 17, 9),
           (4, 256, 4096), (4, 257, 4101), (300, 130, 65), (2, 255, 70), (1, 129, 64),
           (1, 4097, 128), (2, 4095, 190), (1, 2049, 64 * 40), (1, 1025, 64 * 70 - 1), (2, 1024, 64 * 64),
-          (1, 800, 64 * 129), (8, 300, 1000), (2, 520, 72)]
+          (1, 800, 64 * 129), (8, 300, 1000), (2, 520, 72), (20, 200, 830), (20, 128, 1000), (40, 256, 1024),
+          (40, 129, 1024), (5, 512, 3392), (3, 512, 640), (9, 400, 2050), (17, 512, 1024), (17, 513, 1020), (5, 700, 4096),
+          (3, 1025, 990), (10, 1025, 1024), (2, 2049, 4090), (6, 600, 1000), (4, 600, 1000), (4, 1024, 96)]
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
