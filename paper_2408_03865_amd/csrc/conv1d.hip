@@ -457,8 +457,10 @@ __global__ void conv1d_bwd_finalize(const float* __restrict__ partial, float* __
 // 1 x 32768 x 5120 141, 190 and 2 x 65536 x 1024 95, 123; 1 x 16384 x 256 5.1, 7.3 (too few
 // rows); unaligned rows, 8 x 4095 x 4096 119, 121, 2 x 12289 x 2048 43, 46.  In fp32 a lane's 8
 // tokens are two vectors, 32 bytes apart from the next lane's: 182, 223 at 8 x 4096 x 4096.
+// (A launch holds fewer than 2^32 threads.)
 bool conv_fwd_by_row(const ConvArgs& a) {
-    return a.seqlen % kTok == 0 && a.seqlen > 2048 && a.seqlen < 32768 && a.batch * a.dim >= 1024;
+    const int64_t rows = a.batch * a.dim;
+    return a.seqlen % kTok == 0 && a.seqlen > 2048 && a.seqlen < 32768 && rows >= 1024 && rows < (int64_t)1 << 24;
 }
 
 // Rows per lane of the tiled forward where that leaves 8 waves for each of the 1024 SIMDs, else 1.

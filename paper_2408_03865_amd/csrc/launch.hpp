@@ -137,12 +137,12 @@ __host__ __device__ constexpr int64_t dzf_vec(int64_t c, int i, int j) {
 constexpr int kScanBwdChannels = 16;
 
 // Split of the rows into segments along the sequence, each scanned by its own
-// block with the carry across segments resolved by an aggregate pass.  Used only when batch x (channel groups of 16) leaves the GPU underfilled:
-// 256 CUs hold three scan blocks each.  A direction splits when its blocks fill less
+// block with the carry across segments resolved by an aggregate pass.  Used only when
+// batch x (channel groups of 16) leaves the GPU underfilled: 256 CUs hold three scan blocks each.  A direction splits when its blocks fill less
 // than half of its target and then aims at the target: one round of blocks (768) for
 // the forward, two (1536) for the backward, each direction's fastest (4 rows x 2048
-// tokens x 1536 channels, 384 blocks: the forward unsplit takes 102 us against 115 us
-// in 4 segments, while the backward gains from its 4).  More segments never need less
+// tokens x 1536 channels, 384 blocks: the backward gains from 4 segments, the forward does
+// not; what it does with fewer blocks is scan_fwd_plan's).  More segments never need less
 // workspace, so the backward's plan also covers the forward's recompute.
 struct SegPlan {
     int64_t nseg;      // segments per row (1: no split)

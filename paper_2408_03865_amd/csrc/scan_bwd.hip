@@ -15,7 +15,7 @@
 //  4. accumulate du, ddelta per token, dA per lane, and write the dB, dC
 //     contributions; these are summed over the block's 16 channels in LDS and
 //     written as one partial per block (part_bc), summed over blocks by
-//     scan_bwd_finalize_bc in a fixed order.
+//     scan_bwd_finalize in a fixed order.
 // dz needs y, which the forward has computed already: it saves the factor
 // (y + D u) d(z sigmoid(z))/dz of dout beside the chunk states, and dz is written at
 // the start of each chunk, so the state loop does not rebuild y.
@@ -125,8 +125,8 @@ __device__ __forceinline__ void token_step(const T* __restrict__ dr, const int32
     }
 }
 
-// Main pass.  Bound by the VALU issue rate (98% busy at 8 x 4096 x 4096), so what counts
-// is instructions per (token, channel, state): one 16-byte table read per (channel, state)
+// Main pass.  Bound by the VALU issue rate (at 8 x 4096 x 4096 92% busy counted at 2.4 GHz, 98%
+// of the cycles that the clock gave), so what counts is instructions per (token, channel, state): one 16-byte table read per (channel, state)
 // with one address to step, carries that enter the scans at the row's ends, and the dA
 // sums of two states at once took the call from 1920 to 1815 us there (fp32 2120 to 2035).
 // Two channels per lane need 10% fewer instructions and half the dB/dC partials, but 213
@@ -212,6 +212,8 @@ void scan_bwd_kernel(BwdParams p) {
             wf[1] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(fr + dzf_vec(0, 1, 0)));
         }
         // ---- stage B, C, the reset mask and the chunk-start states in LDS ----
+        // The addresses are computed again for each chunk from an index that the compiler cannot
+        // see through: kept over the state loop they would take vector registers that it needs.
         int tids = tid;
         asm volatile("" : "+v"(tids));
         for (int idx = tids * PV; idx < kN * kCH; idx += kThreads * PV) {
@@ -314,7 +316,7 @@ void scan_bwd_kernel(BwdParams p) {
         const float* const red_r = &sm.red[0][0][0][red_which][red_t];
         float* const part_n = p.part_bc + ((b * p.groups + grp) * 2 + red_which) * kN * L + lb;
         float dA_even = 0.0f;
-        // one state; in pairs (ODD: the second), so that the pair shares its address steps
+        // one state; the odd one of a pair also sums the dA of both
 #pragma unroll 1
         for (int n = 0; n < kN; ++n) {
             const f32x4 tb = tab_r[n];
