@@ -452,7 +452,7 @@ __global__ void conv1d_bwd_finalize(const float* __restrict__ partial, float* __
 
 // bf16 rows that a block each walks.  Us, one wave per tile against a block per row:
 // 2 x 6208 x 5120 52, 43; 1 x 7872 x 5120 34, 27; 2 x 16192 x 2048 53, 43; 1 x 21704 x 1536 29,
-// 24; 4 x 3072 x 2048 22, 19; 8 x 4096 x 4096 103, 95.  Beyond the limits, the second measured
+// 24; 4 x 3072 x 2048 22, 19; 5 x 7104 x 192 9.4, 7.3; 8 x 4096 x 4096 103, 95.  Beyond the limits, the second measured
 // with row ends looked for: 12 x 1088 x 5120 62, 68 (a block's 2048 tokens are half empty);
 // 1 x 32768 x 5120 141, 190 and 2 x 65536 x 1024 95, 123; 1 x 16384 x 256 5.1, 7.3 (too few
 // rows); unaligned rows, 8 x 4095 x 4096 119, 121, 2 x 12289 x 2048 43, 46.  In fp32 a lane's 8
@@ -460,7 +460,7 @@ __global__ void conv1d_bwd_finalize(const float* __restrict__ partial, float* __
 // (A launch holds fewer than 2^32 threads.)
 bool conv_fwd_by_row(const ConvArgs& a) {
     const int64_t rows = a.batch * a.dim;
-    return a.seqlen % kTok == 0 && a.seqlen > 2048 && a.seqlen < 32768 && rows >= 1024 && rows < (int64_t)1 << 24;
+    return a.seqlen % kTok == 0 && a.seqlen > 2048 && a.seqlen < 32768 && rows >= 768 && rows < (int64_t)1 << 24;
 }
 
 // Rows per lane of the tiled forward where that leaves 8 waves for each of the 1024 SIMDs, else 1.
@@ -519,23 +519,25 @@ hipError_t conv_fwd_t(const ConvArgs& a, hipStream_t s) {
 }
 
 // Whether a block takes all `parts` waves (batch rows x segments) of a channel.  It sums the
-// parameter gradients and saves the finalize's launch, 2.5 us; but it needs that many free places
-// on one CU at once, which costs where blocks queue, the more so where they load its four SIMDs
-// unevenly, and its waves read batch rows far apart.  Us, a wave per block against gathered, bf16
+// parameter gradients and saves the finalize's launch, 2.5 us; but it needs that many of a CU's 20
+// places at once, which costs where blocks queue, the more so where they load its four SIMDs
+// unevenly or leave many places empty (12), and its waves read batch rows far apart.  Us, a wave per block against gathered, bf16
 // rows of 500 tokens (fp32 and 64 tokens lie within a few percent):
 //   4 waves x 3072 channels 19.9, 17.9; x 5120 28, 27;  5 x 1024 11.5, 10.9; x 1536 14.6, 15.3
 //   6 x 1024 13.3, 12.2; x 1536 16.2, 17.5;  8 x 1024 15.7, 12.7; x 2048 26, 25; x 5120 51, 57
 //   9 x 512 12.2, 11.4; x 1024 16.7, 21.4;  12 x 512 14.6, 12; x 1024 21.8, 23.1
-//   16 x 512 17.4, 13.2; x 1024 28, 27; x 2048 45, 52;  9 x 704 x 5120: 61, 111
+//   16 x 512 17.4, 13.2; x 1024 28, 27; x 2048 45, 52;  9 x 704 x 5120: 61, 111; 12, 4 x 7488 x 403
+//   23.5, 28.8
 // Longer waves: 6 of them, 1 x 4096 x 700 10.8, 8.3; 1 x 8192 x 700 15.5, 15.6; 2 x 3648 x 768 15.7,
-// 18; 14, 1 x 16384 x 300 14.9, 17.8; 16, 16 x 2048 x 256 18.6, 13.3; 8, 8 x 4096 x 512 27, 24.
+//   18; 10, 5 x 1088 x 512 13.2, 14.4; 14, 7 x 1280 x 347 14.1, 16.3; 1 x 16384 x 300 14.9, 17.8;
+//   16, 16 x 2048 x 256 18.6, 13.3; 8, 8 x 4096 x 512 27, 24.
 // Most elements: 2 x 8192 x 2048 45.3, 41.7, fp32 92, 89; 2^26 of them, 4 x 8192 x 2048 77, 79, fp32 177,
 // 182; 8 x 4096 x 4096 157, 188.
 bool conv_bwd_gathers(const ConvArgs& a, int64_t parts) {
     if (parts > kConvBwdParts || a.batch * a.dim * a.seqlen > (int64_t)1 << 25) return false;
     if (parts <= 4) return true;
-    if (parts % 4 == 0) return parts * a.dim <= 8192;
-    return parts * a.dim <= 6144 && a.batch * a.dim * a.seqlen <= (int64_t)1 << 22;
+    if (parts % 8 == 0) return parts * a.dim <= 8192;
+    return parts * a.dim <= (parts < 8 ? 6144 : 4096) && a.batch * a.dim * a.seqlen <= (int64_t)1 << 22;
 }
 
 template <typename T, typename TO, int W, bool DXF>

@@ -96,9 +96,9 @@ def test_conv_forward_lanes_and_tiles(shape, width, dtype):
     _conv_forward(shape, width, dtype)
 
 
-# bf16 rows that a block each walks (aligned, 2049 to 32767 tokens, 1024 rows), and each limit
+# bf16 rows that a block each walks (aligned, 2049 to 32767 tokens, 768 rows), and each limit
 # missed: one row fewer, 2048 tokens, unaligned
-@pytest.mark.parametrize("shape", [(1, 1024, 2056), (4, 257, 4104), (1, 1023, 2056), (2, 520, 2048), (1, 1024, 2060)],
+@pytest.mark.parametrize("shape", [(1, 768, 2056), (4, 257, 4104), (1, 767, 2056), (2, 520, 2048), (1, 1024, 2060)],
                          ids=lambda s: "x".join(map(str, s)))
 @pytest.mark.parametrize("width", [2, 3, 4])
 def test_conv_forward_by_row(shape, width):
@@ -129,11 +129,12 @@ def _conv_forward(shape, width, dtype):
     assert_close("plain", host(plain), O.conv1d_fwd(x, w, None, pos, silu=False), TOL["f32"])
 
 
-# (batch, channels, tokens): waves per channel.  One block gathers up to 4, or up to 16 within
-# 8192 waves in all where they are a multiple of 4, else within 6144 and 2^22 elements: both sides
-# of each limit
+# (batch, channels, tokens): waves per channel.  One block gathers up to 4, 8 or 16 within 8192
+# waves in all, 5 to 7 within 6144 and others up to 16 within 4096, both with 2^22 elements at most:
+# both sides of each limit
 GATHERED = {(1, 3, 70): 1, (3, 5, 1030): 9, (4, 6, 2048): 16, (4, 6, 2049): 20, (17, 4, 30): 17, (4, 1100, 70): 4,
             (6, 1024, 100): 6, (6, 1025, 100): 6, (6, 700, 990): 6, (6, 700, 1000): 6, (8, 1024, 70): 8, (8, 1025, 70): 8,
+            (12, 512, 64): 12, (12, 341, 64): 12, (13, 315, 64): 13, (13, 316, 64): 13, (16, 512, 30): 16, (16, 513, 30): 16,
             (1, 600, 3500): 7, (4, 4100, 2050): 4}
 
 
